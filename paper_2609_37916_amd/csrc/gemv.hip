@@ -1,469 +1,591 @@
-// Dequantising matmul for a few activation rows (the GEMV regime of
-// Op::DequantMatMul, Section VI; Linear block, Section III-A):
+// Matmul for a few activation rows (the GEMV regime of Op::DequantMatMul,
+// Section VI; Linear block, Section III-A):
 //
-//   y[m, n] = epi( sum_k x[m, k] W[n, k] ),   1 <= M <= 16 bf16 rows,
+//   y[m, n] = epi( sum_k x[m, k] W[n, k] ),   1 <= M <= 32 bf16 rows,
 //
-// with W in the int8 per-channel, int4 group-32 zero-point, int8 group-32,
-// int8 group-16 or int4 group-32 min layout (the last three also hold GGUF
-// Q8_0, Q6_K and Q4_1 / Q4_K weights).
+// with W dense bf16 or in any of the quantised layouts (int8 per channel,
+// int4 group-32 zero-point or min, int8 group-32 or group-16; the last four
+// also hold GGUF Q4_0, Q4_1 / Q4_K, Q8_0 and Q6_K weights).
 // With so few rows the product reads every weight byte once and does little
-// arithmetic per byte: it is bound by HBM bandwidth and by the vector-ALU
-// work of unpacking the codes, not by the matrix cores.
+// arithmetic per byte: it is bound by the weight stream, so what matters is
+// how many bytes each CU keeps in flight and how few round trips a block
+// serialises.
 //
-//  * Output columns go in tiles of 16.  Each block takes a contiguous run of
-//    tiles (about two blocks per CU, so the activations are staged once per
-//    block and no second wave of blocks leaves a tail).  Within a tile the 8
-//    waves split K in 128-k units (unit u goes to wave u mod 8); at the end of
-//    the tile the 8 partial 16 x 16 tiles are added in LDS in wave order
-//    (deterministic) and the epilogue is applied.
-//  * Each wave streams its (tile, unit) items through a private ring of LDS
-//    slots with direct-to-LDS loads, two to four items in flight (per
-//    layout, measured) across tile boundaries; the only barrier is the one
-//    per tile that hands the wave partials to the epilogue (double-buffered).
-//    A unit's 16 weight rows land group-major ([16-byte chunk][row][16 B]):
-//    lane (n, G) then reads the 4 (int4) or 8 (int8) bytes of k-octet G of
-//    each group with conflict-free ds_read2.
-//  * v_mfma_f32_16x16x32_bf16 takes the activations as the A operand (rows m;
-//    rows M..15 repeat row M-1 and their results are dropped) and the codes
-//    as B, one 32-k group per instruction.  Lane l supplies row / column
-//    l % 16 and k-octet G = l / 16 of the group; its eight bf16 slots pair
-//    k = 8G + i with 8G + i + 4 (i = 0..3), the pairing the nibble unpacking
-//    yields at the lowest cost.  The activations are stored in LDS in that
-//    order once per block, with the per-group sums X[m, g] = sum_k x[m, k].
-//  * int4: nibble q becomes the bf16 value 128 + q with one AND-OR (0x4300,
-//    the exponent of 128, over the nibble), so a group's instruction gives
-//    V = sum_k x_k (128 + q_k) and the group contributes
-//    s V - s (128 + z) X.  The s V terms are added per group with four FMAs
-//    a lane; the s (128 + z) X terms of four groups are one
-//    v_mfma_f32_16x16x4_f32 (X as A, -s (128 + z) as B).  No weight is
-//    rounded: every rounding is an fp32 sum (the tiled path instead rounds
-//    each (q - z) s to bf16).  int4 min (W = q s + m) is the same with
-//    (m - 128 s) X in place of -s (128 + z) X.
-//  * int8 per-channel: codes convert exactly to bf16 and one accumulator
-//    takes every group; the per-channel scale multiplies the fp32 sum in the
-//    epilogue, as in the tiled path.  int8 group: each group's product is
-//    scaled by its s with four FMAs a lane, as for int4.  int8 group-16: a
-//    32-k instruction would add two groups of different scale, so each group
-//    of 32 takes two instructions, the lanes of the other half (k-octets 2, 3
-//    for the first, 0, 1 for the second) supplying zero codes; each product is
-//    scaled by its own s, as for group 32.
+//  * A block owns 16 CT output columns; its NW waves split K in 128-k units.
+//    A stage (NW units of k) of the activations, weights and scales comes into
+//    an LDS ring by direct-to-LDS loads that follow the rows, so that
+//    consecutive lanes read consecutive bytes.  Loaded straight into registers
+//    in the matrix-core layout every quarter wave touched 16 rows, and the
+//    load units' line rate, not HBM, set the time (int4, 1 x 4096 x 14336: 17.0
+//    us, 16 rows 25.3; through LDS 13.4 and 16.5).
+//  * Each output is the sum of eight partials (unit u in partial u mod 8, in
+//    waves or in accumulator sets of a wave) added in order, so results are
+//    deterministic and a row's bits do not depend on M or on the launch shape.
+//  * v_mfma_f32_16x16x32_bf16 takes the activations as A (row l % 16, k-octet
+//    G = l / 16; rows past M repeat row M-1 and are dropped) and the weights
+//    as B (column l % 16), one 32-k group per instruction.  Every lane reads
+//    16 contiguous bytes of its column's row from LDS.  For int4 those are a whole
+//    group: the 4 x 4 dword transpose over the four lanes of a column that
+//    brings octet G of group q to lane G is four lane-swap instructions
+//    (v_permlane32_swap, v_permlane16_swap).  For int8 they are two octets of
+//    one group; one v_permlane32_swap per dword pair makes an instruction's
+//    four octets one group, in octet order 0, 2, 1, 3, which the activation
+//    addresses follow.  Dense rows and int8 per channel need no exchange (any
+//    k order common to both operands is a valid sum).
+//  * int4: nibble q becomes the bf16 value 128 + q: a byte times 0x1001, then
+//    one AND-OR with the exponent of 128, gives two of them in k order.  A group's
+//    instruction gives V = sum_k x_k (128 + q_k), and the group contributes
+//    s V - s (128 + z) X with X = sum_k x_k (int4 min: s V + (m - 128 s) X).  The
+//    s V terms are added with four FMAs a lane; X comes from products with ones,
+//    laid out so that the other terms of four groups are one
+//    v_mfma_f32_16x16x4_f32.  No weight is rounded: every rounding is an fp32 sum.
+//  * int8 per channel: codes convert exactly to bf16 and one accumulator takes
+//    every group; the scale multiplies the fp32 sum in the epilogue.  int8
+//    group: each group's product is scaled by its s.  int8 group-16: a 32-k
+//    instruction would add two groups of different scale, so each takes two
+//    instructions, the lanes of the other group supplying zero codes.
+//  * In a last unit of 64 k (K an odd multiple of 64) only its two groups are
+//    multiplied; loads past the end of a row repeat the row's last bytes.
+//
+// Measured (MI355X, us per launch among others, weights from HBM; the tiled or
+// earlier few-row kernel / this one):
+//   int4 4096 x 14336, M = 1 12.7 / 12.8, M = 4 199 / 13.5, M = 16 202 / 15.7;
+//   14336 x 4096, M = 1 13.3 / 13.4, M = 16 68.0 / 15.5; int8 4096 x 14336, M = 1
+//   14.5 / 13.4, M = 16 140 / 19.2; dense 4096 x 14336, M = 1 103 / 25 (117 MB at
+//   4.7 TB/s), M = 16 104 / 33.  Loads alone, nothing multiplied: int4 9.9 and 12.1
+//   us at M = 1, so the vector work of unpacking is the rest; it went from ~130 to
+//   ~60 instructions per unit (12.8 from 14.7 us) with the byte multiply and
+//   loop-invariant LDS offsets.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace rlx {
 namespace {
 
-constexpr int kGvWaves = 8;
-constexpr int kGvThreads = kGvWaves * 64;
-constexpr int kGvUnitK = 128;       // k per unit (four 32-k groups)
-constexpr int kGvMaxRows = 16;
-constexpr int kGvMaxXBytes = 64 * 1024;  // activations staged in LDS (bf16)
+constexpr int kSkUnitK = 128;      // k per unit (four 32-k groups)
+constexpr int kSkSplit = 8;        // partial sums of an output: unit u goes to partial u mod 8
+constexpr int kSkMaxRows = 32;
+constexpr int kSkMaxK = 1 << 22;   // lane offsets are 32-bit
 
-template <Quant Q>
-struct GvUnit;
-template <>
-struct GvUnit<Quant::Int4> {
-  // codes: 16 rows x 64 bytes; meta: scales then zeros, 16 rows x 4 f16 each;
-  // kDepth items in flight per wave (measured on the 14336 x 4096 product:
-  // 2 in flight 12.0 us, 3 13.3 us, 4 14.0 us)
-  static constexpr int kCodeBytes = 1024, kMetaBytes = 256, kLoads = 2, kDepth = 2;
-};
-template <>
-struct GvUnit<Quant::Int4M> : GvUnit<Quant::Int4> {};  // zeros hold the mins
-template <>
-struct GvUnit<Quant::Int8G> {
-  // codes: 16 rows x 128 bytes; meta: 16 rows x 4 f16 scales (then a copy)
-  static constexpr int kCodeBytes = 2048, kMetaBytes = 256, kLoads = 3, kDepth = 3;
-};
-template <>
-struct GvUnit<Quant::Int8G16> {
-  // codes: 16 rows x 128 bytes; meta: 16 rows x 8 f16 scales
-  static constexpr int kCodeBytes = 2048, kMetaBytes = 256, kLoads = 3, kDepth = 3;
-};
-template <>
-struct GvUnit<Quant::Int8> {
-  // (2 in flight 14.2 us, 3 14.0 us, 4 13.6 us)
-  static constexpr int kCodeBytes = 2048, kMetaBytes = 0, kLoads = 2, kDepth = 4;
-};
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+
+// 16-byte weight loads a lane makes per unit and column tile.
+__host__ __device__ constexpr int sk_loads(Quant q) { return q == Quant::None ? 4 : quant_int8(q) ? 2 : 1; }
+__host__ __device__ constexpr int sk_meta_bytes(Quant q) { return q == Quant::Int8G16 ? 16 : 8; }  // scale bytes per unit
+__host__ __device__ constexpr bool sk_grouped(Quant q) { return q != Quant::None && q != Quant::Int8; }
+constexpr bool sk_swapped(Quant q) { return q == Quant::Int8G || q == Quant::Int8G16; }
 
 __device__ __forceinline__ float f16_lo(uint32_t v) { return f16_bits_to_f32((uint16_t)(v & 0xffffu)); }
 __device__ __forceinline__ float f16_hi(uint32_t v) { return f16_bits_to_f32((uint16_t)(v >> 16)); }
 
-// Eight int4 codes (k = 8G + 0..7 in nibble order) -> bf16 (128 + q) in the
-// slot order (i, i + 4): dword i holds nibble i in its low half and nibble
-// i + 4 in its high half.  `mask` (0x000F000F) and `exp` (0x43004300) come in
-// registers: a VOP3 instruction on gfx950 takes no literal operand, so with
-// literal masks each (a & mask) | exp becomes two instructions instead of one
-// v_and_or_b32.
-__device__ __forceinline__ bf16x8_t int4_octet_as_offset_bf16(uint32_t w, uint32_t mask, uint32_t exp) {
-  return as_bf16x8(make_uint4((w & mask) | exp, ((w >> 4) & mask) | exp, ((w >> 8) & mask) | exp,
-                              ((w >> 12) & mask) | exp));
+// The upper 32 lanes of a change places with the lower 32 lanes of b.
+__device__ __forceinline__ void swap_lanes32(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+// Rows 1 and 3 of 16 lanes of a change places with rows 0 and 2 of b.
+__device__ __forceinline__ void swap_lanes16(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
 }
 
-// Eight int8 codes (k = 8G + 0..3 in lo, 4..7 in hi) -> bf16 (exact) in the
-// slot order (i, i + 4).
+// Direct-to-LDS loads from a wave-uniform base and a lane's byte offset.
+__device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t off, uint32_t lds_addr) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
+               : "memory", "m0");
+#pragma clang diagnostic pop
+}
+__device__ __forceinline__ void lds_dma4_at(const uint8_t* base, uint32_t off, uint32_t lds_addr) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
+               : "memory", "m0");
+#pragma clang diagnostic pop
+}
+
+// Eight int4 codes (k ascending, low nibble first) -> bf16 (128 + q), k
+// ascending.  A byte times 0x1001 holds its low nibble at bit 0 and its high
+// nibble at bit 16; one AND-OR keeps those and puts the exponent of 128 over
+// them.  `mask` (0x000F000F) and `exp` (0x43004300) come in registers: a VOP3
+// instruction on gfx950 takes no literal operand, so with literal masks each
+// (a & mask) | exp becomes two instructions instead of one v_and_or_b32.
+__device__ __forceinline__ bf16x8_t int4_octet_as_offset_bf16(uint32_t w, uint32_t mask, uint32_t exp) {
+  uint32_t o[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) o[j] = ((((w >> (8 * j)) & 0xffu) * 0x1001u) & mask) | exp;
+  return as_bf16x8(make_uint4(o[0], o[1], o[2], o[3]));
+}
+
+// Eight int8 codes (k ascending over lo, hi) -> bf16, exact.
 __device__ __forceinline__ bf16x8_t int8_octet_as_bf16(uint32_t lo, uint32_t hi) {
+  const uint32_t w[2] = {lo, hi};
   uint32_t o[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float a = (float)(int8_t)(lo >> (8 * i));
-    const float b = (float)(int8_t)(hi >> (8 * i));
+    const uint32_t v = w[i >> 1] >> (16 * (i & 1));
+    const float a = (float)(int8_t)v, b = (float)(int8_t)(v >> 8);
     o[i] = __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u);  // (a, b) upper halves
   }
   return as_bf16x8(make_uint4(o[0], o[1], o[2], o[3]));
 }
 
-// Epilogue operands of a block's run of tpb tiles in LDS (byte offsets);
-// every part is 256-byte aligned, the whole a multiple of 1 KB.
-struct GvEpiLayout {
-  int bias, scale, res, res_pitch, bytes;
-};
-__host__ __device__ constexpr int gv_round(int v, int a) { return (v + a - 1) / a * a; }
-// (residual rows of y's element size: 2 bytes, or 4 for an f32 output)
-__host__ __device__ inline GvEpiLayout gv_epi_layout(Quant q, Epi e, int M, int tpb, bool y_f32) {
-  GvEpiLayout l{};
-  int off = 0;
-  l.bias = off;
-  if (e != Epi::None) off += gv_round(tpb * 16 * 4, 256);
-  l.scale = off;
-  if (q == Quant::Int8) off += gv_round(tpb * 16 * 2, 256);
-  l.res = off;
-  l.res_pitch = gv_round(tpb * 16 * (y_f32 ? 4 : 2), 256);
-  if (e == Epi::BiasResidual) off += M * l.res_pitch;
-  l.bytes = gv_round(off, 1024);
-  return l;
+// sum_k x[m,k] W[n,k] term by term, each weight formed in fp32.  The kernel's
+// sums over codes (x_k (128 + q_k), x_k q_k) can pass the fp32 range, or meet
+// an infinity of the other sign, where the product itself does not: an output
+// that is not finite is computed again this way.
+template <Quant Q>
+__device__ __forceinline__ float sk_direct(const GemmParams& p, int m, int n) {
+  const int K = p.K;
+  const bf16_t* x = reinterpret_cast<const bf16_t*>(p.x) + (size_t)m * K;
+  const uint8_t* w = reinterpret_cast<const uint8_t*>(p.w) + (size_t)n * (quant_int4(Q) ? K / 2 : K);
+  constexpr int GS = Q == Quant::Int8G16 ? 16 : 32;
+  const uint16_t* sc = reinterpret_cast<const uint16_t*>(p.scales) + (size_t)n * (K / GS);
+  const uint16_t* zp = quant_int4(Q) ? reinterpret_cast<const uint16_t*>(p.zeros) + (size_t)n * (K / GS) : nullptr;
+  float v = 0.0f;
+#pragma unroll 1
+  for (int k = 0; k < K; ++k) {
+    const float s = f16_bits_to_f32(sc[k / GS]);
+    float wk;
+    if constexpr (quant_int4(Q)) {
+      const float q = (float)((k & 1) ? w[k / 2] >> 4 : w[k / 2] & 0xf), z = f16_bits_to_f32(zp[k / GS]);
+      wk = Q == Quant::Int4 ? (q - z) * s : fmaf(q, s, z);
+    } else {
+      wk = (float)(int8_t)w[k] * s;
+    }
+    v = fmaf(bf16_to_f32(x[k]), wk, v);
+  }
+  return v;
 }
 
-template <Quant Q, Epi E>
-__global__ __launch_bounds__(kGvThreads) void gemv_q_kernel(GemmParams p) {
-  using U = GvUnit<Q>;
-  extern __shared__ __attribute__((aligned(16))) uint8_t gv_lds[];
+// LDS of a stage (NW units of k): activations [MR][128 NW] bf16, weights
+// [16 CT][row bytes], scales (then zeros) [16 CT][dwords].
+struct SkStage {
+  int w, m, bytes;
+};
+__host__ __device__ constexpr SkStage sk_stage(Quant q, int MR, int CT, int NW) {
+  SkStage s{};
+  s.w = MR * NW * kSkUnitK * 2;
+  s.m = s.w + 16 * CT * sk_loads(q) * 64 * NW;
+  s.bytes = s.m + (sk_grouped(q) ? 16 * CT * sk_meta_bytes(q) * NW * (quant_int4(q) ? 2 : 1) : 0);
+  return s;
+}
+
+// MR: activation rows staged (1, 2, 4, 8, 16 or 32; rows past M repeat row M - 1).
+// S: stages in the ring.
+template <Quant Q, int MR, int CT, int NW, int S>
+__global__ __launch_bounds__(NW * 64) void skinny_gemm_kernel(GemmParams p) {
+  constexpr int MT = MR > 16 ? 2 : 1;
+  constexpr int NE = MR < 4 ? MR : 4;  // accumulator registers that hold a row of x (up to 4 rows: of lanes 0..15)
+  constexpr int NSET = kSkSplit / NW;  // accumulator sets: a wave's stages go to them in turn
+  constexpr int CL = sk_loads(Q), BK = NW * kSkUnitK;
+  constexpr int WROW = CL * 64 * NW;                 // weight bytes of a row per stage
+  constexpr int GROW = sk_meta_bytes(Q) * NW;        // scale bytes of a row per stage
+  constexpr int WB = 16 * CT * WROW / 1024 / NW;     // 1 KB weight blocks a wave moves per stage
+  constexpr int MBA = 16 * CT * GROW / 256;          // 256-byte blocks of a scale array (scales, zeros)
+  constexpr int MBT = sk_grouped(Q) ? MBA * (quant_int4(Q) ? 2 : 1) : 0;
+  constexpr int MB = (MBT + NW - 1) / NW;            // of which a wave moves so many (the last ones twice)
+  constexpr int XBYTES = MR <= 2 ? 256 : 1024;       // one or two rows: dword loads, so that every wave moves a part
+  constexpr int XB = MR * BK * 2 / XBYTES / NW;
+  constexpr int LPS = WB + MB + XB;                  // loads of a wave per stage
+  constexpr SkStage L = sk_stage(Q, MR, CT, NW);
+  static_assert(XB >= 1 && WB >= 1 && MBA >= 1 && (S - 2) * LPS < 64, "whole blocks, vmcnt range");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int M = p.M, N = p.N, K = p.K;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, G = lane >> 4;
-  const int units = K / kGvUnitK;
-  const int nu = units > wave ? (units - wave + kGvWaves - 1) / kGvWaves : 0;  // this wave's units per tile
-  // this block's tiles of 16 columns: t0 .. t0 + nt - 1
-  const int tiles = N / 16;
-  const int tpb = (tiles + gridDim.x - 1) / gridDim.x;
-  const int t0 = blockIdx.x * tpb;
-  const int nt = max(0, min(tiles - t0, tpb));
-  const int items = nt * nu;  // (tile, unit) items of this wave, tile-major
+  const int n0 = blockIdx.x * (16 * CT);
+  const int units = (K + kSkUnitK - 1) / kSkUnitK;
+  const int KT = (K + BK - 1) / BK;
 
-  // LDS: code slots [kGvWaves][kDepth] | int4 scale/zero slots [kGvWaves][kDepth]
-  //      | wave partials [2][kGvWaves][64 lanes][4] f32 | epilogue operands of
-  //      the block's tiles (GvEpiLayout) | activations [K/8][M][16 B]
-  //      | group sums [K/32][M] f32   (direct-to-LDS destinations 256-byte aligned)
-  uint8_t* ring = gv_lds + wave * U::kDepth * U::kCodeBytes;
-  uint8_t* meta = gv_lds + kGvWaves * U::kDepth * U::kCodeBytes + wave * U::kDepth * U::kMetaBytes;
-  uint8_t* red = gv_lds + kGvWaves * U::kDepth * (U::kCodeBytes + U::kMetaBytes);
-  const GvEpiLayout el = gv_epi_layout(Q, E, M, tpb, p.y_f32);
-  uint8_t* epi = red + 2 * kGvWaves * 1024;
-  uint8_t* xl = epi + el.bytes;
-  float* xs = reinterpret_cast<float*>(xl + (size_t)M * K * 2);
-
-  // 1. Activations, as stored, into LDS.
-  constexpr int kOctPerThread = kGvMaxXBytes / 16 / kGvThreads;
-  const int octets = M * K / 8;  // 16-byte octets of x, a multiple of 16
-  const int oct_per_row = K / 8;
-  const uint32_t xl_addr = lds_addr_of(xl);
+  // Epilogue operands first: they land while the weights stream.
+  constexpr int OPT = (MT * CT * 256 + NW * 64 - 1) / (NW * 64);  // outputs per thread
+  // (kept as loaded: a conversion here would wait for them)
+  float bias[OPT];
+  uint32_t res[OPT], chs[OPT];
 #pragma unroll
-  for (int i = 0; i < kOctPerThread; ++i) {
-    const int q0 = wave * 64 + i * kGvThreads;  // octet of lane 0 in this load
-    if (q0 < octets && q0 + lane < octets)
-      lds_dma16(reinterpret_cast<const bf16_t*>(p.x) + (size_t)(q0 + lane) * 8,
-                __builtin_amdgcn_readfirstlane(xl_addr + q0 * 16));
+  for (int o = 0; o < OPT; ++o) {
+    const int idx = tid + o * NW * 64;
+    const int m = idx / (16 * CT), n = n0 + idx % (16 * CT);
+    bias[o] = 0.0f;
+    res[o] = chs[o] = 0;
+    if (m < M) {
+      if (p.epi != Epi::None) bias[o] = p.bias[n];
+      if (Q == Quant::Int8) chs[o] = reinterpret_cast<const uint16_t*>(p.scales)[n];
+      if (p.epi == Epi::BiasResidual) {
+        if (p.y_f32)
+          res[o] = reinterpret_cast<const uint32_t*>(p.residual)[(size_t)m * N + n];
+        else
+          res[o] = reinterpret_cast<const bf16_t*>(p.residual)[(size_t)m * N + n];
+      }
+    }
   }
 
-  // Epilogue operands of the block's tiles (bias, int8 scales, residual
-  // rows), 4 bytes a lane: each wave moves the rows m = wave mod 8 of the
-  // residual; wave 0 the bias, wave 1 the scales.
-  const int ncol = nt * 16;  // this block's columns, from column 16 t0
-  auto dma_run = [&](const void* src, uint8_t* dst, int dwords) {
-    for (int j = 0; j * 64 < dwords; ++j)
-      if (j * 64 + lane < dwords)
-        lds_dma4(reinterpret_cast<const uint32_t*>(src) + j * 64 + lane,
-                 __builtin_amdgcn_readfirstlane(lds_addr_of(dst) + j * 256));
-  };
-  if constexpr (E != Epi::None)
-    if (wave == 0) dma_run(p.bias + (size_t)t0 * 16, epi + el.bias, ncol);
-  if constexpr (Q == Quant::Int8)
-    if (wave == 1) dma_run(reinterpret_cast<const uint16_t*>(p.scales) + (size_t)t0 * 16, epi + el.scale, ncol / 2);
-  if constexpr (E == Epi::BiasResidual)
-    for (int m = wave; m < M; m += kGvWaves) {
-      if (p.y_f32)
-        dma_run(reinterpret_cast<const float*>(p.residual) + (size_t)m * N + (size_t)t0 * 16,
-                epi + el.res + m * el.res_pitch, ncol);
+  // Per-lane sources: the byte offset of the lane's row and the lane's byte
+  // within the stage's part of it.  Past the end of a row (a last partial
+  // stage) lanes fetch the row's last bytes, which nothing multiplies.  LDS
+  // rows hold their 16-byte chunks XOR-swizzled by row mod 16 (the low four
+  // bits of the chunk index; the source address is permuted, the LDS address
+  // is linear): a quarter wave's fragment read, one chunk of 16 rows, then
+  // covers all banks.
+  const uint32_t wpitch = Q == Quant::None ? K * 2 : quant_int4(Q) ? K / 2 : K;
+  const uint32_t gpitch = K / (Q == Quant::Int8G16 ? 16 : 32) * 2;
+  const uint8_t* wbase = reinterpret_cast<const uint8_t*>(p.w) + (size_t)n0 * wpitch;
+  const uint8_t* xbase = reinterpret_cast<const uint8_t*>(p.x);
+  const uint8_t* sbase = reinterpret_cast<const uint8_t*>(p.scales) + (MB > 0 ? (size_t)n0 * gpitch : 0);
+  const uint8_t* zbase = reinterpret_cast<const uint8_t*>(p.zeros) + (MBT > MBA ? (size_t)n0 * gpitch : 0);
+  uint32_t wrow[WB], wcol[WB], xrow[XB], xcol[XB], mrow[MB ? MB : 1], mcol[MB ? MB : 1];
+#pragma unroll
+  for (int i = 0; i < WB; ++i) {
+    const int b = (wave + i * NW) * 1024 + lane * 16;  // byte of the stage's weights
+    const int r = b / WROW;
+    wcol[i] = (b % WROW) ^ ((r & 15) * 16);
+    wrow[i] = r * wpitch;
+  }
+#pragma unroll
+  for (int i = 0; i < XB; ++i) {
+    const int b = (wave + i * NW) * XBYTES + lane * (XBYTES / 64);
+    const int r = b / (BK * 2);
+    xcol[i] = (b % (BK * 2)) ^ ((r & 15) * 16);
+    xrow[i] = (uint32_t)min(r, M - 1) * (K * 2);
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int b = (wave + i * NW) % MBT % MBA * 256 + lane * 4;
+    mcol[i] = b % GROW;
+    mrow[i] = b / GROW * gpitch;
+  }
+  const uint32_t lds0 = lds_addr_of(lds);
+  const bool partial = K % BK != 0;
+  auto issue = [&](int kt, int buf) {
+    const uint32_t base = lds0 + buf * L.bytes;
+    const bool edge = partial && kt == KT - 1;
+#pragma unroll
+    for (int i = 0; i < WB; ++i) {
+      uint32_t c = wcol[i];
+      if (edge) c = min(c, wpitch - 16 - kt * WROW);
+      lds_dma16_at(wbase + (size_t)kt * WROW, wrow[i] + c, __builtin_amdgcn_readfirstlane(base + L.w + (wave + i * NW) * 1024));
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const int blk = (wave + i * NW) % MBT;
+      uint32_t c = mcol[i];
+      if (edge) c = min(c, gpitch - 4 - kt * GROW);
+      lds_dma4_at((blk < MBA ? sbase : zbase) + (size_t)kt * GROW, mrow[i] + c,
+                  __builtin_amdgcn_readfirstlane(base + L.m + blk * 256));
+    }
+#pragma unroll
+    for (int i = 0; i < XB; ++i) {
+      uint32_t c = xcol[i];
+      if (edge) c = min(c, (uint32_t)(K * 2 - XBYTES / 64 - kt * (BK * 2)));
+      const uint32_t dst = __builtin_amdgcn_readfirstlane(base + (wave + i * NW) * XBYTES);
+      if constexpr (XBYTES == 1024)
+        lds_dma16_at(xbase + (size_t)kt * (BK * 2), xrow[i] + c, dst);
       else
-        dma_run(reinterpret_cast<const bf16_t*>(p.residual) + (size_t)m * N + (size_t)t0 * 16,
-                epi + el.res + m * el.res_pitch, ncol / 2);
+        lds_dma4_at(xbase + (size_t)kt * (BK * 2), xrow[i] + c, dst);
     }
-
-  // 2. Item loads.  Item (tile t, unit u): lane (row l16, chunk G) of the
-  //    wave moves 16 bytes of row 16 t + l16; slot layout [chunk][row][16 B].
-  const size_t wpitch = quant_int4(Q) ? (size_t)K / 2 : (size_t)K;
-  const uint8_t* wlane = reinterpret_cast<const uint8_t*>(p.w) + (size_t)l16 * wpitch + G * 16;
-  // int4 scales and zeros ([N][K/32] f16): lanes < 32 move the scales of row
-  // lane/2, the others the zeros of row (lane-32)/2, two groups (4 bytes) each
-  // (int8 group scales: every lane moves scales, lanes >= 32 a second copy;
-  // group 16 ([N][K/16] f16): lane moves two of the eight scales of row lane/4)
-  constexpr bool kG16 = Q == Quant::Int8G16;
-  const size_t gpitch = (size_t)K / (kG16 ? 16 : 32) * 2;
-  const uint8_t* mlane =
-      U::kMetaBytes == 0 ? nullptr
-      : kG16 ? reinterpret_cast<const uint8_t*>(p.scales) + (size_t)(lane >> 2) * gpitch + (lane & 3) * 4
-             : reinterpret_cast<const uint8_t*>(lane < 32 || Q == Quant::Int8G ? p.scales : p.zeros) +
-                   (size_t)((lane & 31) >> 1) * gpitch + (lane & 1) * 4;
-  const uint32_t ring_addr = lds_addr_of(ring), meta_addr = lds_addr_of(meta);
-  auto issue = [&](int i) {
-    const int tt = i / nu, u = wave + (i - tt * nu) * kGvWaves;
-    const size_t row0 = (size_t)(t0 + tt) * 16;
-    const uint32_t slot = ring_addr + (uint32_t)((i % U::kDepth) * U::kCodeBytes);
-    if constexpr (quant_int4(Q)) {
-      lds_dma16(wlane + row0 * wpitch + (size_t)u * 64, __builtin_amdgcn_readfirstlane(slot));
-    } else {
-      lds_dma16(wlane + row0 * wpitch + (size_t)u * 128, __builtin_amdgcn_readfirstlane(slot));
-      lds_dma16(wlane + row0 * wpitch + (size_t)u * 128 + 64, __builtin_amdgcn_readfirstlane(slot + 1024));
-    }
-    if constexpr (U::kMetaBytes > 0)
-      lds_dma4(mlane + row0 * gpitch + (size_t)u * (kG16 ? 16 : 8),
-               __builtin_amdgcn_readfirstlane(meta_addr + (uint32_t)((i % U::kDepth) * U::kMetaBytes)));
   };
-  // The activations are waited for before any item load goes out.  (Issuing
-  // the first items before that wait measured the same within 0.5 us: the
-  // activations then queue behind other blocks' weight bytes instead.)
-  wait_vmcnt<0>();
-  const int pro = min(items, U::kDepth);
-  for (int i = 0; i < pro; ++i) issue(i);
 
-  // 3. Activations rewritten in place in slot order ([K/8][M][16 B], bf16
-  //    pairs (i, i + 4) of each octet), and the per-group sums.
-  uint4 xr[kOctPerThread];
-#pragma unroll
-  for (int i = 0; i < kOctPerThread; ++i) {
-    const int q = tid + i * kGvThreads;
-    if (q < octets) xr[i] = *reinterpret_cast<const uint4*>(xl + (size_t)q * 16);
-  }
-  __syncthreads();  // every stored octet is in registers before any is overwritten
-#pragma unroll
-  for (int i = 0; i < kOctPerThread; ++i) {
-    const int q = tid + i * kGvThreads;
-    if (q < octets) {  // uniform over the 4 lanes of a group
-      const int m = q / oct_per_row, o = q - m * oct_per_row;
-      const uint4 v = xr[i];
-      const uint4 e = make_uint4(__builtin_amdgcn_perm(v.z, v.x, 0x05040100u), __builtin_amdgcn_perm(v.z, v.x, 0x07060302u),
-                                 __builtin_amdgcn_perm(v.w, v.y, 0x05040100u), __builtin_amdgcn_perm(v.w, v.y, 0x07060302u));
-      *reinterpret_cast<uint4*>(xl + ((size_t)o * M + m) * 16) = e;
-      const uint32_t d[4] = {v.x, v.y, v.z, v.w};
-      float t = 0.0f;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) t += __uint_as_float(d[j] << 16) + __uint_as_float(d[j] & 0xffff0000u);
-      // the group's four octets sit on lanes 4a .. 4a+3 (quad_perm xor 1, then xor 2)
-      t += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0xB1, 0xF, 0xF, false));
-      t += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, t), 0x4E, 0xF, 0xF, false));
-      if ((q & 3) == 0) xs[(o >> 2) * M + m] = t;
-    }
-  }
-  __syncthreads();
-
-  // 4. Tiles: K loop per tile, then the wave partials to the epilogue.
-  const int mc = min(l16, M - 1);  // A-operand row of this lane
   const f32x4_t zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4_t acc[NSET][MT][CT];
+#pragma unroll
+  for (int e = 0; e < NSET; ++e)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) acc[e][mt][ct] = zero4;
   // nibble pair mask and the bf16 exponent of 128, as register values the
   // compiler cannot fold back into literals (see int4_octet_as_offset_bf16)
-  uint32_t kMask, kExp;
-  asm volatile("v_mov_b32 %0, 0x000F000F" : "=v"(kMask));
-  asm volatile("v_mov_b32 %0, 0x43004300" : "=v"(kExp));
-  for (int tt = 0; tt < nt; ++tt) {
-    f32x4_t acc = zero4;
-    for (int j = 0; j < nu; ++j) {
-      const int i = tt * nu + j;
-      wait_stage<U::kLoads, U::kDepth - 1>(min(items - 1 - i, U::kDepth - 1));  // item i has landed
-      const int u = wave + j * kGvWaves;
-      const uint8_t* slot = ring + (i % U::kDepth) * U::kCodeBytes;
-      const uint8_t* mslot = meta + (i % U::kDepth) * U::kMetaBytes;
-      bf16x8_t xa[4];
+  uint32_t kMask = 0, kExp = 0;
+  if constexpr (quant_int4(Q)) {
+    asm volatile("v_mov_b32 %0, 0x000F000F" : "=v"(kMask));
+    asm volatile("v_mov_b32 %0, 0x43004300" : "=v"(kExp));
+  }
+  // group sums: rows 4q .. 4q + 3 of the A operand are ones for group q, so the
+  // four products added up leave X of group G in every register of lane (m, G)
+  bf16x8_t sel[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        xa[q] = as_bf16x8(*reinterpret_cast<const uint4*>(xl + ((size_t)(16 * u + 4 * q + G) * M + mc) * 16));
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t v = (l16 >> 2) == q ? 0x3f803f80u : 0u;
+    sel[q] = as_bf16x8(make_uint4(v, v, v, v));
+  }
+  const bf16x8_t zb = as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
+  // octet of this lane in group q: see the header
+  const int oct = sk_swapped(Q) ? (G >> 1) | ((G & 1) << 1) : G;
+
+  // This lane's LDS bytes within a stage (the unrolled loop below adds the
+  // stage's offset as an immediate).
+  uint32_t xoff[MT][4], coff[CT][CL];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int m = min(mt * 16 + l16, MR - 1);
+      // 16-byte chunk of the row: 16 chunks per unit
+      const int ch = wave * 16 + (Q == Quant::Int8 ? (q >> 1) * 8 + G * 2 + (q & 1) : q * 4 + oct);
+      xoff[mt][q] = m * (BK * 2) + ((ch ^ (m & 15)) * 16);
+    }
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int j = 0; j < CL; ++j) {
+      const int r = ct * 16 + l16;
+      coff[ct][j] = L.w + r * WROW + (((wave * CL + j) * 4 + G) ^ (r & 15)) * 16;
+    }
+  const uint32_t moff = L.m + l16 * GROW + wave * sk_meta_bytes(Q);
+
+  // Multiplies this wave's unit of the stage: NG groups (4, or the 2 of a half unit).
+  auto unit = [&](auto groups, const uint8_t* st, f32x4_t (&acc)[MT][CT], auto&& prefetch) {
+    constexpr int NG = decltype(groups)::value;
+    uint4 xr[MT][NG], c[CT][CL];
+    u32x4_t s[CT];
+    uint16_t sg[CT], zg[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+      for (int j = 0; j < CL; ++j)
+        if (NG == 4 || j == 0 || j < CL / 2) c[ct][j] = *reinterpret_cast<const uint4*>(st + coff[ct][j]);
+      const uint8_t* ms = st + moff + ct * 16 * GROW;
+      if constexpr (Q == Quant::Int8G16) {
+        s[ct] = *reinterpret_cast<const u32x4_t*>(ms);
+      } else if constexpr (sk_grouped(Q)) {
+        const u32x2_t v = *reinterpret_cast<const u32x2_t*>(ms);
+        s[ct].x = v.x;
+        s[ct].y = v.y;
+      }
       if constexpr (quant_int4(Q)) {
-        const uint32_t* cw = reinterpret_cast<const uint32_t*>(slot + l16 * 16 + G * 4);
-        const uint32_t c0 = cw[0], c1 = cw[64], c2 = cw[128], c3 = cw[192];
-        const uint2 sv = *reinterpret_cast<const uint2*>(mslot + l16 * 8);
-        const uint16_t zg = *reinterpret_cast<const uint16_t*>(mslot + 128 + l16 * 8 + G * 2);
-        const uint16_t sg = *reinterpret_cast<const uint16_t*>(mslot + l16 * 8 + G * 2);
-        const float xsum = xs[(4 * u + G) * M + mc];
-        wait_lgkmcnt0();
-        if (i + U::kDepth < items) issue(i + U::kDepth);  // the slot's bytes are all in registers
-        const f32x4_t v0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[0], int4_octet_as_offset_bf16(c0, kMask, kExp), zero4, 0, 0, 0);
-        const f32x4_t v1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[1], int4_octet_as_offset_bf16(c1, kMask, kExp), zero4, 0, 0, 0);
-        const f32x4_t v2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[2], int4_octet_as_offset_bf16(c2, kMask, kExp), zero4, 0, 0, 0);
-        const f32x4_t v3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[3], int4_octet_as_offset_bf16(c3, kMask, kExp), zero4, 0, 0, 0);
-        // int4: s V - s (128 + z) X;  int4 min (zg holds m): s V + (m - 128 s) X
-        const float negc = Q == Quant::Int4 ? -f16_bits_to_f32(sg) * (128.0f + f16_bits_to_f32(zg))
-                                            : fmaf(-128.0f, f16_bits_to_f32(sg), f16_bits_to_f32(zg));
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xsum, negc, acc, 0, 0, 0);
-        const float s0 = f16_lo(sv.x), s1 = f16_hi(sv.x), s2 = f16_lo(sv.y), s3 = f16_hi(sv.y);
+        sg[ct] = *reinterpret_cast<const uint16_t*>(ms + G * 2);
+        zg[ct] = *reinterpret_cast<const uint16_t*>(ms + 16 * CT * GROW + G * 2);
+      }
+    }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = fmaf(s0, v0[r], fmaf(s1, v1[r], fmaf(s2, v2[r], fmaf(s3, v3[r], acc[r]))));
-      } else if constexpr (Q == Quant::Int8G) {
-        const uint2* cw = reinterpret_cast<const uint2*>(slot + (G >> 1) * 256 + l16 * 16 + (G & 1) * 8);
-        const uint2 c0 = cw[0], c1 = cw[64], c2 = cw[128], c3 = cw[192];
-        const uint2 sv = *reinterpret_cast<const uint2*>(mslot + l16 * 8);
-        wait_lgkmcnt0();
-        if (i + U::kDepth < items) issue(i + U::kDepth);
-        const f32x4_t v0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[0], int8_octet_as_bf16(c0.x, c0.y), zero4, 0, 0, 0);
-        const f32x4_t v1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[1], int8_octet_as_bf16(c1.x, c1.y), zero4, 0, 0, 0);
-        const f32x4_t v2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[2], int8_octet_as_bf16(c2.x, c2.y), zero4, 0, 0, 0);
-        const f32x4_t v3 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[3], int8_octet_as_bf16(c3.x, c3.y), zero4, 0, 0, 0);
-        const float s0 = f16_lo(sv.x), s1 = f16_hi(sv.x), s2 = f16_lo(sv.y), s3 = f16_hi(sv.y);
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = fmaf(s0, v0[r], fmaf(s1, v1[r], fmaf(s2, v2[r], fmaf(s3, v3[r], acc[r]))));
+      for (int q = 0; q < NG; ++q) xr[mt][q] = *reinterpret_cast<const uint4*>(st + xoff[mt][q]);
+    prefetch();
+    bf16x8_t xa[MT][NG];
+    float X[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      f32x4_t xs = zero4;
+#pragma unroll
+      for (int q = 0; q < NG; ++q) {
+        xa[mt][q] = as_bf16x8(xr[mt][q]);
+        if constexpr (quant_int4(Q)) xs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel[q], xa[mt][q], xs, 0, 0, 0);
+      }
+      X[mt] = xs[0];  // (zero for the groups a half unit lacks)
+    }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      bf16x8_t b[NG];
+      if constexpr (quant_int4(Q)) {
+        uint32_t t[4] = {c[ct][0].x, c[ct][0].y, c[ct][0].z, c[ct][0].w};
+        swap_lanes32(t[0], t[2]);
+        swap_lanes32(t[1], t[3]);
+        swap_lanes16(t[0], t[1]);
+        swap_lanes16(t[2], t[3]);
+#pragma unroll
+        for (int q = 0; q < NG; ++q) b[q] = int4_octet_as_offset_bf16(t[q], kMask, kExp);
+      } else if constexpr (Q == Quant::None) {
+#pragma unroll
+        for (int q = 0; q < NG; ++q) b[q] = as_bf16x8(c[ct][q]);
+      } else {
+#pragma unroll
+        for (int h = 0; h < NG / 2; ++h) {
+          uint32_t t[4] = {c[ct][h].x, c[ct][h].y, c[ct][h].z, c[ct][h].w};
+          if constexpr (sk_swapped(Q)) {
+            swap_lanes32(t[0], t[2]);
+            swap_lanes32(t[1], t[3]);
+          }
+          b[2 * h] = int8_octet_as_bf16(t[0], t[1]);
+          b[2 * h + 1] = int8_octet_as_bf16(t[2], t[3]);
+        }
+      }
+      if constexpr (!sk_grouped(Q)) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int q = 0; q < NG; ++q)
+            acc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][q], b[q], acc[mt][ct], 0, 0, 0);
       } else if constexpr (Q == Quant::Int8G16) {
-        const uint2* cw = reinterpret_cast<const uint2*>(slot + (G >> 1) * 256 + l16 * 16 + (G & 1) * 8);
-        const uint2 c0 = cw[0], c1 = cw[64], c2 = cw[128], c3 = cw[192];
-        const uint4 sv = *reinterpret_cast<const uint4*>(mslot + l16 * 16);
-        wait_lgkmcnt0();
-        if (i + U::kDepth < items) issue(i + U::kDepth);
-        // group 2q (k 32q .. 32q + 15) is k-octets 0, 1 of instruction q, group 2q + 1 octets 2, 3
-        const bool first = G < 2;
-        const bf16x8_t zb = as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
-        const uint2 cc[4] = {c0, c1, c2, c3};
-        const uint32_t sw[4] = {sv.x, sv.y, sv.z, sv.w};
+        const bool first = (G & 1) == 0;  // lanes of octets 0, 1 (octet order 0, 2, 1, 3)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const bf16x8_t b = int8_octet_as_bf16(cc[q].x, cc[q].y);
-          const f32x4_t va = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[q], first ? b : zb, zero4, 0, 0, 0);
-          const f32x4_t vb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[q], first ? zb : b, zero4, 0, 0, 0);
-          const float sa = f16_lo(sw[q]), sb = f16_hi(sw[q]);
+        for (int q = 0; q < NG; ++q) {
+          const float sa = f16_lo(s[ct][q]), sb = f16_hi(s[ct][q]);
+          const bf16x8_t ba = first ? b[q] : zb, bb = first ? zb : b[q];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) acc[r] = fmaf(sa, va[r], fmaf(sb, vb[r], acc[r]));
+          for (int mt = 0; mt < MT; ++mt) {
+            const f32x4_t va = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][q], ba, zero4, 0, 0, 0);
+            const f32x4_t vb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][q], bb, zero4, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) acc[mt][ct][e] = fmaf(sa, va[e], fmaf(sb, vb[e], acc[mt][ct][e]));
+          }
         }
       } else {
-        const uint2* cw = reinterpret_cast<const uint2*>(slot + (G >> 1) * 256 + l16 * 16 + (G & 1) * 8);
-        const uint2 c0 = cw[0], c1 = cw[64], c2 = cw[128], c3 = cw[192];
-        wait_lgkmcnt0();
-        if (i + U::kDepth < items) issue(i + U::kDepth);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[0], int8_octet_as_bf16(c0.x, c0.y), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[1], int8_octet_as_bf16(c1.x, c1.y), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[2], int8_octet_as_bf16(c2.x, c2.y), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[3], int8_octet_as_bf16(c3.x, c3.y), acc, 0, 0, 0);
-      }
-    }
-    // The partials of tile tt go to buffer tt % 2: the epilogue of tile tt - 2,
-    // the last reader of that buffer, ran before the barrier of tile tt - 1.
-    uint8_t* rb = red + (tt & 1) * kGvWaves * 1024;
-    *reinterpret_cast<f32x4_t*>(rb + wave * 1024 + lane * 16) = acc;
-    __syncthreads();
-    if (tid < 16 * kGvMaxRows) {
-      const int m = tid >> 4, n = (t0 + tt) * 16 + (tid & 15);
-      if (m < M) {  // output (m, n) is register m % 4 of lane n % 16 + 16 (m / 4)
-        const int src = ((tid & 15) + 16 * (m >> 2)) * 16 + (m & 3) * 4;
-        float v = 0.0f;
+        if constexpr (quant_int4(Q)) {
+          // this lane's group: -s (128 + z), int4 min m - 128 s (a half unit's
+          // missing groups: X is zero there, and the other factor must be finite)
+          const bool has = NG == 4 || G < 2;
+          const float sl = has ? f16_bits_to_f32(sg[ct]) : 0.0f, zl = has ? f16_bits_to_f32(zg[ct]) : 0.0f;
+          const float f = Q == Quant::Int4 ? -sl * (128.0f + zl) : fmaf(-128.0f, sl, zl);
 #pragma unroll
-        for (int w = 0; w < kGvWaves; ++w) v += *reinterpret_cast<const float*>(rb + w * 1024 + src);
-        const int c = tt * 16 + (tid & 15);  // column within the block's run
-        if constexpr (Q == Quant::Int8) v *= f16_bits_to_f32(reinterpret_cast<const uint16_t*>(epi + el.scale)[c]);
-        if constexpr (E != Epi::None) v += reinterpret_cast<const float*>(epi + el.bias)[c];
-        if constexpr (E == Epi::BiasGelu) v = gelu_erf(v);
-        if constexpr (E == Epi::BiasResidual)
-          v += p.y_f32 ? reinterpret_cast<const float*>(epi + el.res + m * el.res_pitch)[c]
-                       : bf16_to_f32(reinterpret_cast<const bf16_t*>(epi + el.res + m * el.res_pitch)[c]);
-        if (p.y_f32)
-          reinterpret_cast<float*>(p.y)[(size_t)m * N + n] = v;
+          for (int mt = 0; mt < MT; ++mt)
+            acc[mt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(X[mt], f, acc[mt][ct], 0, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+          const uint32_t sv = q < 2 ? s[ct].x : s[ct].y;
+          const float sq = (q & 1) == 0 ? f16_lo(sv) : f16_hi(sv);
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            const f32x4_t v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[mt][q], b[q], zero4, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < NE; ++e) acc[mt][ct][e] = fmaf(sq, v[e], acc[mt][ct][e]);
+          }
+        }
+      }
+    }
+  };
+
+#pragma unroll
+  for (int st = 0; st < S - 1; ++st)
+    if (st < KT) issue(st, st);
+  // unrolled over the ring (two stages: also over the accumulator sets), so that
+  // a stage's LDS offsets are immediates
+  constexpr int UN = NSET == 1 || S % 2 == 0 ? S : 2 * S;
+  for (int kt0 = 0; kt0 < KT; kt0 += UN) {
+#pragma unroll
+    for (int i = 0; i < UN; ++i) {
+      const int kt = kt0 + i;
+      if (kt < KT) {
+        wait_stage<LPS, S - 2>(min(S - 2, KT - 1 - kt));
+        __syncthreads();  // stage kt visible to all waves; the buffer of stage kt - 1 is free
+        const int u = kt * NW + wave;
+        const uint8_t* st = lds + (i % S) * L.bytes;
+        auto prefetch = [&] {
+          if (kt + S - 1 < KT) issue(kt + S - 1, (i + S - 1) % S);
+        };
+        if (u + 1 < units || (u < units && (K & 64) == 0))
+          unit(std::integral_constant<int, 4>{}, st, acc[i % NSET], prefetch);
+        else if (u < units)
+          unit(std::integral_constant<int, 2>{}, st, acc[i % NSET], prefetch);
         else
-          reinterpret_cast<bf16_t*>(p.y)[(size_t)m * N + n] = f32_to_bf16(v);
+          prefetch();
       }
     }
   }
-}
 
-// Compute units of the current device (cached per device).
-int device_cus() {
-  static int cached[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (!cached[dev]) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cached[dev] = n;
+  // The eight partials, added in order.  Output (m, n) of a 16 x 16 tile is
+  // register m % 4 of lane n + 16 (m / 4).
+  __syncthreads();  // the stages are no longer read
+#pragma unroll
+  for (int e = 0; e < NSET; ++e)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+        *reinterpret_cast<f32x4_t*>(lds + (((e * NW + wave) * MT * CT + mt * CT + ct) * 64 + lane) * 16) = acc[e][mt][ct];
+  __syncthreads();
+#pragma unroll
+  for (int o = 0; o < OPT; ++o) {
+    const int idx = tid + o * NW * 64;
+    const int m = idx / (16 * CT), c = idx % (16 * CT), n = n0 + c;
+    if (m >= M || idx >= MT * CT * 256) continue;
+    const int tile = (m >> 4) * CT + (c >> 4);
+    const uint8_t* src = lds + (tile * 64 + (c & 15) + 16 * ((m & 15) >> 2)) * 16 + (m & 3) * 4;
+    float v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kSkSplit; ++w) v += *reinterpret_cast<const float*>(src + w * MT * CT * 1024);
+    if constexpr (Q == Quant::Int8) v *= f16_bits_to_f32((uint16_t)chs[o]);
+    if constexpr (sk_grouped(Q))
+      if (!(fabsf(v) <= 3.402823466e38f)) v = sk_direct<Q>(p, m, n);
+    v += bias[o];
+    if (p.epi == Epi::BiasGelu) v = gelu_erf(v);
+    v += __uint_as_float(p.y_f32 ? res[o] : res[o] << 16);
+    if (p.y_f32)
+      reinterpret_cast<float*>(p.y)[(size_t)m * N + n] = v;
+    else
+      reinterpret_cast<bf16_t*>(p.y)[(size_t)m * N + n] = f32_to_bf16(v);
   }
-  return cached[dev];
 }
 
-struct GvPlan {
-  int grid, tpb;
-  size_t lds;
-};
-
-// Up to two blocks per CU (as many as the LDS allows), each with an equal run
-// of tpb 16-column tiles; the LDS holds the rings, the wave partials, the
-// run's epilogue operands and the activations.
-GvPlan gemv_plan(const GemmParams& p) {
-  using U4 = GvUnit<Quant::Int4>;
-  using U8 = GvUnit<Quant::Int8>;
-  using U8G = GvUnit<Quant::Int8G>;
-  using U8G16 = GvUnit<Quant::Int8G16>;
-  const int ring = quant_int4(p.quant)            ? U4::kDepth * (U4::kCodeBytes + U4::kMetaBytes)
-                   : p.quant == Quant::Int8G     ? U8G::kDepth * (U8G::kCodeBytes + U8G::kMetaBytes)
-                   : p.quant == Quant::Int8G16   ? U8G16::kDepth * (U8G16::kCodeBytes + U8G16::kMetaBytes)
-                                                 : U8::kDepth * (U8::kCodeBytes + U8::kMetaBytes);
-  const size_t base = (size_t)kGvWaves * ring + 2 * kGvWaves * 1024 + (size_t)p.M * p.K * 2 +
-                      (size_t)p.M * (p.K / 32) * 4;
-  const int tiles = p.N / 16;
-  GvPlan g{};
-  for (int per_cu = 2; per_cu >= 1; --per_cu) {
-    g.tpb = (tiles + device_cus() * per_cu - 1) / (device_cus() * per_cu);
-    g.lds = base + gv_epi_layout(p.quant, p.epi, p.M, g.tpb, p.y_f32).bytes;
-    if (g.lds * per_cu <= 160 * 1024) break;
-  }
-  g.grid = (tiles + g.tpb - 1) / g.tpb;
-  return g;
-}
-
-template <Quant Q, Epi E>
-hipError_t launch_gemv_typed(const GemmParams& p, hipStream_t s) {
-  const GvPlan g = gemv_plan(p);
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_q_kernel<Q, E>),
+template <Quant Q, int MR, int CT, int NW, int S>
+hipError_t launch_skinny(const GemmParams& p, hipStream_t s) {
+  constexpr SkStage L = sk_stage(Q, MR, CT, NW);
+  constexpr int lds = std::max(S * L.bytes, kSkSplit * (MR > 16 ? 2 : 1) * CT * 1024);
+  static_assert(lds <= 160 * 1024, "LDS of a workgroup");
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_gemm_kernel<Q, MR, CT, NW, S>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
-  RLX_LOG_LAUNCH("gemv_q_kernel", dim3(g.grid), dim3(kGvThreads), g.lds, "few-row %s epi=%s M=%d N=%d K=%d",
-                 quant_name(Q), epi_name(E), p.M, p.N, p.K);
-  hipLaunchKernelGGL((gemv_q_kernel<Q, E>), dim3(g.grid), dim3(kGvThreads), g.lds, s, p);
+  RLX_LOG_LAUNCH("skinny_gemm_kernel", dim3(p.N / (16 * CT)), dim3(NW * 64), lds,
+                 "few-row %s epi=%s rows=%d cols=%d stages=%d M=%d N=%d K=%d", quant_name(Q), epi_name(p.epi), MR,
+                 CT * 16, S, p.M, p.N, p.K);
+  hipLaunchKernelGGL((skinny_gemm_kernel<Q, MR, CT, NW, S>), dim3(p.N / (16 * CT)), dim3(NW * 64), lds, s, p);
   return hipGetLastError();
 }
 
+// Two launch shapes, by how many 16-column tiles there are for the 256 CUs.
+// Few tiles: one tile per 8-wave block, three stages in flight or being read.
+// Many tiles: two tiles per 4-wave block, two stages, three or more blocks per
+// CU whose round trips and epilogues overlap.  Measured (us, few / many, one
+// launch among others, weights from HBM):
+//   int4  M = 1:  N x K 4096 x 4096 6.2 / 8.8, 11008 x 4096 11.5 / 12.7, 14336 x 4096 14.0 / 13.2
+//   int4  M = 16: 4096 x 4096 7.5 / 9.9, 6144 x 4096 12.0 / 10.3, 14336 x 4096 22.9 / 14.9
+//   int8  M = 32: 4096 x 4096 10.6 / 12.3, 6144 x 4096 17.4 / 12.8, 14336 x 4096 33.0 / 24.4
+// so many above 256 tiles, with up to 4 rows (little to share between the two
+// tiles) above 768.  Dense rows are long enough for one tile per block, and
+// with 17 rows or more the first shape wins at every N (14336 x 4096, M = 32:
+// 34.9 / 41.9).  A deeper ring is slower (int4 M = 1, 4096 x 14336: 3 stages
+// 13.4, 6 14.9, 13 16.2 us).
+template <Quant Q, int MR>
+hipError_t launch_skinny_q(const GemmParams& p, hipStream_t s) {
+  constexpr int kLds = 160 * 1024;
+  constexpr SkStage L8 = sk_stage(Q, MR, 1, 8);
+  const bool many = p.N / 16 > (MR <= 4 ? 768 : 256) && !(Q == Quant::None && MR > 16);
+  if (many) return launch_skinny<Q, MR, Q == Quant::None ? 1 : 2, 4, 2>(p, s);
+  if constexpr (2 * L8.bytes <= kLds)
+    return launch_skinny<Q, MR, 1, 8, 3 * L8.bytes <= kLds ? 3 : 2>(p, s);
+  else  // 32 rows of dense or group-16 weights: stages of half the k
+    return launch_skinny<Q, MR, 1, 4, 3>(p, s);
+}
+
 template <Quant Q>
-hipError_t launch_gemv_q(const GemmParams& p, hipStream_t s) {
-  switch (p.epi) {
-    case Epi::None: return launch_gemv_typed<Q, Epi::None>(p, s);
-    case Epi::Bias: return launch_gemv_typed<Q, Epi::Bias>(p, s);
-    case Epi::BiasGelu: return launch_gemv_typed<Q, Epi::BiasGelu>(p, s);
-    case Epi::BiasResidual: return launch_gemv_typed<Q, Epi::BiasResidual>(p, s);
-  }
-  return hipErrorInvalidValue;
+hipError_t launch_skinny_rows(const GemmParams& p, hipStream_t s) {
+  if (p.M == 1) return launch_skinny_q<Q, 1>(p, s);
+  if (p.M == 2) return launch_skinny_q<Q, 2>(p, s);
+  if (p.M <= 4) return launch_skinny_q<Q, 4>(p, s);
+  if (p.M <= 8) return launch_skinny_q<Q, 8>(p, s);
+  if (p.M <= 16) return launch_skinny_q<Q, 16>(p, s);
+  return launch_skinny_q<Q, 32>(p, s);
 }
 
 }  // namespace
 
 bool gemv_supported(const GemmParams& p) {
   auto a4 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 3) == 0; };
-  return p.quant != Quant::None && p.dtype == DType::BF16 && p.m_dev == nullptr &&
-         p.x_head_rows == 0 && !p.x_stats && !p.res_stats && !p.y_stats && p.M >= 1 && p.M <= kGvMaxRows &&
-         p.N % 16 == 0 && p.K % kGvUnitK == 0 && (size_t)p.M * p.K * 2 <= (size_t)kGvMaxXBytes &&
-         a4(p.scales) && (!quant_int4(p.quant) || a4(p.zeros)) && gemv_plan(p).lds <= 160 * 1024;
+  return p.dtype == DType::BF16 && p.m_dev == nullptr && p.x_head_rows == 0 && !p.x_stats && !p.res_stats &&
+         !p.y_stats && p.M >= 1 && p.M <= kSkMaxRows && p.N % 64 == 0 && p.K % 64 == 0 && p.K >= kSkUnitK &&
+         p.K <= kSkMaxK && (p.quant == Quant::None || (a4(p.scales) && (!quant_int4(p.quant) || a4(p.zeros))));
 }
 
 hipError_t launch_gemv(const GemmParams& p, hipStream_t s) {
   if (!gemv_supported(p)) return hipErrorInvalidValue;
   switch (p.quant) {
-    case Quant::Int4: return launch_gemv_q<Quant::Int4>(p, s);
-    case Quant::Int4M: return launch_gemv_q<Quant::Int4M>(p, s);
-    case Quant::Int8: return launch_gemv_q<Quant::Int8>(p, s);
-    case Quant::Int8G: return launch_gemv_q<Quant::Int8G>(p, s);
-    case Quant::Int8G16: return launch_gemv_q<Quant::Int8G16>(p, s);
-    default: return hipErrorInvalidValue;
+    case Quant::None: return launch_skinny_rows<Quant::None>(p, s);
+    case Quant::Int4: return launch_skinny_rows<Quant::Int4>(p, s);
+    case Quant::Int4M: return launch_skinny_rows<Quant::Int4M>(p, s);
+    case Quant::Int8: return launch_skinny_rows<Quant::Int8>(p, s);
+    case Quant::Int8G: return launch_skinny_rows<Quant::Int8G>(p, s);
+    case Quant::Int8G16: return launch_skinny_rows<Quant::Int8G16>(p, s);
   }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace rlx

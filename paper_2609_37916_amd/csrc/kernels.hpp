@@ -101,10 +101,10 @@ hipError_t launch_dequant_jobs(const DequantJob* jobs, int njobs, int max_elems,
 enum GemmTile : int { kTileAuto = 0, kTile128x128 = 1, kTile64x128 = 2, kTile64x64 = 3, kTile128x64 = 4 };
 hipError_t launch_gemm(const GemmParams& p, hipStream_t s);
 
-// Few-row dequantising matmul (gemv.hip): int8 / int4 weights, bf16 x with
-// 1 <= M <= 16 rows, N % 16 == 0, K % 128 == 0, M * K * 2 <= 64 KB, 4-byte
-// aligned scales and zeros, no device-side row count and no deferred-LayerNorm fields.  launch_gemm takes
-// this path by itself whenever it applies.
+// Few-row matmul (gemv.hip): dense bf16 or quantised weights, bf16 x with
+// 1 <= M <= 32 rows, N and K multiples of 64, 128 <= K <= 2^22, 4-byte aligned
+// scales and zeros, no device-side row count and no deferred-LayerNorm fields.
+// launch_gemm takes this path by itself whenever it applies.
 bool gemv_supported(const GemmParams& p);
 hipError_t launch_gemv(const GemmParams& p, hipStream_t s);
 

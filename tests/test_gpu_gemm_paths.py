@@ -254,3 +254,71 @@ def test_f32_output_elementwise(rlx, case, epi):
         s_k = np.repeat(W.scales.astype(np.float64), 32, axis=1)
         tol = tol + 2.0 ** -9 * (np.abs(x.astype(np.float64)) @ s_k.T)
     assert_within(got, ref, tol, f"f32 output {case} {epi} {M}x{N}x{K}")
+
+
+# The few-row kernel's edges: row counts around its 1 / 4 / 8 / 16 / 32-row
+# layouts; K of one unit, a half unit after it, part of a stage, whole stages
+# and a half unit, more stages than the ring holds; N on both sides of the
+# launch-shape rule (256 and 768 tiles of 16 columns).
+FEW_ROW_SHAPES = [(1, 64, 128), (2, 128, 192), (5, 64, 1024), (9, 128, 1216), (17, 64, 4160), (32, 64, 640),
+                  (1, 64, 4096), (16, 4160, 576), (32, 4160, 320), (4, 12352, 704), (3, 4160, 128)]
+
+
+@pytest.mark.parametrize("scheme", SCHEMES + ["dense"])
+@pytest.mark.parametrize("M,N,K", FEW_ROW_SHAPES)
+def test_few_rows(rlx, scheme, M, N, K):
+    """fp32 sums of exact operands: the accumulation bound, and for the int4
+    forms the offset terms' 2^-9 sum_k |x_k| (|s| + |m|) of the few-row tests
+    (int8 groups and group-16 scale exact group sums, inside the accumulation
+    bound); a row's bits are the same alone and among others."""
+    rng = np.random.default_rng(100 + M + N + K)
+    x = to_bf16_exact(rng.normal(0, 1, (M, K)))
+    b = rng.normal(0, 0.5, N).astype(np.float32)
+    r = rng.normal(0, 1, (M, N)).astype(np.float32)
+    W = w = None
+    if scheme == "dense":
+        w = to_bf16_exact(rng.normal(0, 0.05, (N, K)))
+
+        def run(rows):
+            y = rlx.dequant_matmul(_dev(x[rows], torch.bfloat16), _dev(w, torch.bfloat16), bias=_dev(b, torch.float32),
+                                   residual=_dev(r[rows], torch.float32), epi=rlx.EPI_BIAS_RESIDUAL,
+                                   out_dtype=torch.float32)
+            torch.cuda.synchronize()
+            return y.cpu().numpy()
+    else:
+        W = Weights(scheme, N, K, seed=200 + M + N + K)
+        w = W.w
+
+        def run(rows):
+            return W.run(rlx, x[rows], bias=b, residual=r[rows], epi="residual", out_dtype=torch.float32).cpu().numpy()
+    got = run(slice(None))
+    ref = oracle.linear(x, w, b) + r
+    tol = gemm_tolerance(x, w, ref, out_bf16=False) + 2.0 ** -24 * np.abs(ref) * 4
+    if scheme in ("int4", "int4m"):
+        off = np.abs(W.scales.astype(np.float64)) + (np.abs(W.zeros.astype(np.float64)) if scheme == "int4m" else 0)
+        tol = tol + 2.0 ** -9 * (np.abs(x.astype(np.float64)) @ np.repeat(off, 32, axis=1).T)
+    assert_within(got, ref, tol, f"few rows {scheme} {M}x{N}x{K}")
+    one = run(slice(M - 1, M))
+    assert np.array_equal(one[0].view(np.uint32), got[M - 1].view(np.uint32))
+
+
+@pytest.mark.parametrize("scheme", SCHEMES)
+def test_few_rows_infinite_and_huge_activations(rlx, scheme):
+    """An infinite activation, and finite ones whose products with the codes
+    pass the fp32 range, give what the weights' own product gives: infinities
+    of the weight's sign, finite values where the sum is finite (int8 per
+    channel: the scale multiplies the fp32 sum over codes, on every path, so
+    only its infinities are fixed)."""
+    M, N, K = 3, 64, 320
+    W = Weights(scheme, N, K, seed=11)
+    x = np.zeros((M, K), np.float32)
+    x[0, 37] = np.inf
+    x[1, 40] = 2.0 ** 125
+    x[2, 41] = 1.0
+    got = W.run(rlx, x, out_dtype=torch.float32).cpu().numpy()
+    with np.errstate(invalid="ignore", over="ignore"):
+        want = np.where(W.w[:, 37] == 0, np.nan, np.sign(W.w[:, 37]) * np.inf)
+        assert np.array_equal(got[0], want.astype(np.float32), equal_nan=True)
+    if scheme != "int8":
+        assert np.allclose(got[1], W.w[:, 40] * 2.0 ** 125, rtol=2.0 ** -20, atol=0)
+    assert np.all(np.isfinite(got[2]))
