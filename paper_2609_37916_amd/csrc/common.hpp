@@ -224,6 +224,22 @@ __device__ __forceinline__ void lds_dma4(const void* g, uint32_t lds_addr) {
 #pragma clang diagnostic pop
 }
 
+// Direct-to-LDS loads from a wave-uniform base and a lane's byte offset.
+__device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t off, uint32_t lds_addr) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
+               : "memory", "m0");
+#pragma clang diagnostic pop
+}
+__device__ __forceinline__ void lds_dma4_at(const uint8_t* base, uint32_t off, uint32_t lds_addr) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
+               : "memory", "m0");
+#pragma clang diagnostic pop
+}
+
 // Wait until at most N vector-memory operations of this wave are outstanding.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {

@@ -1,0 +1,436 @@
+// Large-tile GEMM with fused epilogues, for products with enough rows to fill
+// the CUs with 256-row or 128-row tiles:  y[m,n] = epi( sum_k x[m,k] W[n,k] ),
+// bf16 activations, W dense bf16 or quantised codes (Linear block, Section
+// III-A; Op::DequantMatMul, Sections III-A and VI).
+//
+// What bounds a tiled GEMM here is the rate at which a CU brings operands in
+// from L2 (about 20 bytes per clock when other CUs stream too, 45 to 52 when
+// everything is L2-resident): a 64 x 128 tile needs 96 bytes per clock at the
+// matrix cores' peak, 256 x 256 needs 32.  So the tile is as large as LDS and
+// registers allow, and the order of tiles keeps an XCD's tiles in a compact
+// rectangle that shares operand rows through its L2.
+//
+//  * Eight waves in a WMW x WNW grid, each with BM/WMW x BN/WNW outputs in
+//    32 x 32 accumulators (weights as the A operand: a lane ends up with one
+//    output row and four consecutive columns per register quad).
+//  * Operands come by direct-to-LDS loads in stages of 64 k (128-byte rows,
+//    16-byte chunks XOR-swizzled by (row / 2) mod 8) into a ring of S stages.
+//    The fragments of the next 16-k chunk are read while the matrix cores work
+//    on this one, across stages too: before the last chunk of a stage the
+//    block waits for the next stage, meets once, refills the buffer whose
+//    fragments are all in registers, and reads on.
+//  * Quantised codes travel as codes and become bf16 as fragments are read
+//    (int8 per channel exactly, its scale on the fp32 sum; the group schemes
+//    formed in fp32 and rounded once), as in the smaller tiles.
+//  * Epilogue: each wave stages 32 rows of its accumulators in LDS at a time
+//    and writes whole 16-byte chunks of output rows.
+//
+// Measured (MI355X, us, the smaller tiles / these): dense 2048 x 14336 x 4096 516 /
+// 241 (1.0 PFLOP/s), 2048 x 4096 x 14336 506 / 208 (1.16 PFLOP/s), 509 x 14336 x 4096
+// 144 / 63; int8 509 x 14336 x 4096 168 / 68, 509 x 4096 x 14336 145 / 104; int4
+// 509 x 14336 x 4096 466 / 89, 2048 x 14336 x 4096 1859 / 340.  With the loads taken
+// out of the loop the 2048-row dense products take 198 and 159 us, with the LDS
+// reads out too 173 and 136: the matrix cores' own time at this clock, then LDS,
+// then the operand stream.
+#include <algorithm>
+
+#include "common.hpp"
+#include "dequant.hpp"
+#include "kernels.hpp"
+
+namespace rlx {
+namespace {
+
+constexpr int kBigThreads = 512;
+
+__device__ __forceinline__ uint4 ldq(const void* p) { return *reinterpret_cast<const uint4*>(p); }
+__device__ __forceinline__ int big_swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+
+// Weight bytes of a row per 64-k stage.
+__host__ __device__ constexpr int big_wbytes(Quant q) { return q == Quant::None ? 128 : quant_int8(q) ? 64 : 32; }
+__host__ __device__ constexpr int big_stage_bytes(int BM, int BN, Quant q) { return BM * 128 + BN * big_wbytes(q); }
+
+// Group scales (and zeros / mins) come for 256 k at a time, two such blocks in
+// LDS: bytes of a row and array, arrays.
+__host__ __device__ constexpr int big_mbytes(Quant q) { return q == Quant::Int8G16 ? 32 : 16; }
+__host__ __device__ constexpr int big_marrays(Quant q) {
+  return q == Quant::None || q == Quant::Int8 ? 0 : quant_int4(q) ? 2 : 1;
+}
+__host__ __device__ constexpr int big_meta_bytes(int BN, Quant q) { return BN * big_mbytes(q) * big_marrays(q); }
+
+// A weight fragment (8 k of a row) as it travels.
+template <Quant Q> struct RawFrag { typedef uint2 type; };
+template <> struct RawFrag<Quant::None> { typedef uint4 type; };
+template <> struct RawFrag<Quant::Int4> { typedef uint32_t type; };
+template <> struct RawFrag<Quant::Int4M> { typedef uint32_t type; };
+
+// Tile of block `bid`: XCD bid % 8 takes a contiguous run of tiles, numbered
+// down the rows of a band of four row tiles, then along its columns, so that
+// the tiles an XCD works on at once form a compact rectangle.
+__device__ __forceinline__ void big_tile(int bid, int m_tiles, int n_tiles, int& mt, int& nt) {
+  constexpr int kBand = 4;
+  const int total = m_tiles * n_tiles, q8 = total >> 3, r8 = total & 7, xcd = bid & 7;
+  const int t = xcd * q8 + min(xcd, r8) + (bid >> 3);
+  const int band = t / (kBand * n_tiles), r = t - band * kBand * n_tiles;
+  const int rows = min(kBand, m_tiles - band * kBand);
+  mt = band * kBand + r % rows;
+  nt = r / rows;
+}
+
+template <int BM, int BN, int WMW, int WNW, int S, Quant Q>
+__global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
+  constexpr int NW = WMW * WNW;
+  static_assert(NW * 64 == kBigThreads, "eight waves");
+  constexpr int WM = BM / WMW, WN = BN / WNW;
+  constexpr int TM = WM / 32, TN = WN / 32;
+  static_assert(TM >= 1 && TN >= 1 && S >= 2, "tile");
+  constexpr int WB = big_wbytes(Q);
+  constexpr int kStage = big_stage_bytes(BM, BN, Q);
+  constexpr int XI = BM / 8 / NW;              // 1 KB activation blocks per wave and stage
+  constexpr int WBT = BN * WB / 1024;          // 1 KB weight blocks per stage
+  constexpr int WI = (WBT + NW - 1) / NW;      // of which a wave moves so many (four blocks: each twice)
+  constexpr int LPS = XI + WI;
+  constexpr int MA = big_marrays(Q), MROW = big_mbytes(Q), MBYTES = big_meta_bytes(BN, Q);
+  constexpr int MBT = MA > 0 ? MBYTES / 256 : 1;  // 256-byte scale blocks per 256 k
+  constexpr int MI = (MBT + NW - 1) / NW;      // of which a wave moves so many (the last ones twice)
+  static_assert(MA == 0 || S <= 4, "scales requested with stage kt + S are older than stage kt + 4");
+  static_assert(BM / 8 % NW == 0 && (WBT % NW == 0 || NW % WBT == 0) && (S - 1) * LPS < 64, "whole blocks, vmcnt range");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+
+  const int M = p.M, N = p.N, K = p.K;
+  const int m_tiles = (M + BM - 1) / BM, n_tiles = (N + BN - 1) / BN;
+  int mt, nt;
+  big_tile(blockIdx.x, m_tiles, n_tiles, mt, nt);
+  const int m0 = mt * BM, n0 = nt * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WNW, wn = wave % WNW;
+  const int l32 = lane & 31, half = lane >> 5;
+  const int KT = K / 64;
+
+  // Lane offsets of the loads from wave-uniform bases; rows past M or N repeat
+  // the last row (nothing is stored for them).
+  const uint32_t xpitch = K * 2, wpitch = K / 64 * WB;
+  const uint8_t* xbase = reinterpret_cast<const uint8_t*>(p.x) + (size_t)m0 * xpitch;
+  const uint8_t* wbase = reinterpret_cast<const uint8_t*>(p.w) + (size_t)n0 * wpitch;
+  uint32_t xo[XI], wo[WI];
+#pragma unroll
+  for (int i = 0; i < XI; ++i) {
+    const int row = 8 * (wave + i * NW) + (lane >> 3);
+    xo[i] = min(row, M - 1 - m0) * xpitch + big_swz(row, lane & 7) * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < WI; ++i) {
+    const int b = (wave + i * NW) % WBT * 1024 + lane * 16, row = b / WB, ch = b % WB / 16;
+    const int c = Q == Quant::None ? big_swz(row, ch) : quant_int8(Q) ? ch ^ ((row >> 2) & 3) : ch ^ ((row >> 3) & 1);
+    wo[i] = min(row, N - 1 - n0) * wpitch + c * 16;
+  }
+  const uint32_t lds0 = lds_addr_of(smem);
+  const uint32_t gpitch = K / (Q == Quant::Int8G16 ? 16 : 32) * 2;
+  const uint8_t* sbase = reinterpret_cast<const uint8_t*>(p.scales) + (MA > 0 ? (size_t)n0 * gpitch : 0);
+  const uint8_t* zbase = reinterpret_cast<const uint8_t*>(p.zeros) + (MA > 1 ? (size_t)n0 * gpitch : 0);
+  // Scales of k 256 g .. 256 g + 255 into block g mod 2 (past the end of a row
+  // its last ones again).
+  [[maybe_unused]] auto issue_meta = [&](int g) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int blk = (wave + i * NW) % MBT, b = blk * 256 + lane * 4;
+      const int row = b % (BN * MROW) / MROW;
+      const uint32_t c = min((uint32_t)(g * MROW + b % MROW), gpitch - 4);
+      lds_dma4_at(blk * 256 < BN * MROW ? sbase : zbase, min(row, N - 1 - n0) * gpitch + c,
+                  __builtin_amdgcn_readfirstlane(lds0 + S * kStage + (g & 1) * MBYTES + blk * 256));
+    }
+  };
+  auto issue = [&](int kt, int slot) {
+    const uint32_t base = lds0 + slot * kStage;
+#pragma unroll
+    for (int i = 0; i < XI; ++i)
+      lds_dma16_at(xbase + (size_t)kt * 128, xo[i], __builtin_amdgcn_readfirstlane(base + (wave + i * NW) * 1024));
+#pragma unroll
+    for (int i = 0; i < WI; ++i)
+      lds_dma16_at(wbase + (size_t)kt * WB, wo[i], __builtin_amdgcn_readfirstlane(base + BM * 128 + (wave + i * NW) % WBT * 1024));
+  };
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < TN; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+
+  // Fragment bytes of chunk q (16 k) within a stage; tiles of 32 rows further
+  // down are at fixed distances, with the same swizzle.
+  const int xr = wm * WM + l32, wr = wn * WN + l32;
+  auto read_x = [&](const uint8_t* st, int q, bf16x8_t (&f)[TM]) {
+#pragma unroll
+    for (int t = 0; t < TM; ++t) f[t] = as_bf16x8(ldq(st + xr * 128 + big_swz(xr, 2 * q + half) * 16 + t * 32 * 128));
+  };
+  typedef typename RawFrag<Q>::type raw_t;
+  auto read_w = [&](const uint8_t* st, int q, raw_t (&f)[TN]) {
+    const uint8_t* ws = st + BM * 128;
+#pragma unroll
+    for (int t = 0; t < TN; ++t) {
+      if constexpr (Q == Quant::None)
+        f[t] = ldq(ws + wr * 128 + big_swz(wr, 2 * q + half) * 16 + t * 32 * 128);
+      else if constexpr (quant_int8(Q))
+        f[t] = *reinterpret_cast<const uint2*>(ws + wr * 64 + (q ^ ((wr >> 2) & 3)) * 16 + half * 8 + t * 32 * 64);
+      else
+        f[t] = *reinterpret_cast<const uint32_t*>(ws + wr * 32 + ((q >> 1) ^ ((wr >> 3) & 1)) * 16 + (q & 1) * 8 + half * 4 +
+                                                  t * 32 * 32);
+    }
+  };
+  // The scales of a stage's 64 k: two f16 a row (group-16: four), and zeros.
+  uint2 sc[TN];
+  uint32_t zp[TN];
+  auto read_meta = [&](int kt) {
+    if constexpr (MA > 0) {
+      const uint8_t* ms = smem + S * kStage + ((kt >> 2) & 1) * MBYTES + wr * MROW + (kt & 3) * (MROW / 4);
+#pragma unroll
+      for (int t = 0; t < TN; ++t) {
+        if constexpr (Q == Quant::Int8G16)
+          sc[t] = *reinterpret_cast<const uint2*>(ms + t * 32 * MROW);
+        else
+          sc[t].x = *reinterpret_cast<const uint32_t*>(ms + t * 32 * MROW);
+        if constexpr (MA > 1) zp[t] = *reinterpret_cast<const uint32_t*>(ms + BN * MROW + t * 32 * MROW);
+      }
+    }
+  };
+  auto f16_at = [](uint32_t v, int i) { return f16_bits_to_f32((uint16_t)(v >> (16 * i))); };
+  auto weight = [&](raw_t f, int t, int q) {
+    if constexpr (Q == Quant::None)
+      return as_bf16x8(f);
+    else if constexpr (Q == Quant::Int8)
+      return int8x8_to_bf16(f);
+    else if constexpr (Q == Quant::Int8G16)
+      return int8x8_scaled_to_bf16(f, f16_at(q < 2 ? sc[t].x : sc[t].y, q & 1));
+    else if constexpr (Q == Quant::Int8G)
+      return int8x8_scaled_to_bf16(f, f16_at(sc[t].x, q >> 1));
+    else
+      return int4x8_to_bf16<Q>(f, f16_at(sc[t].x, q >> 1), f16_at(zp[t], q >> 1));
+  };
+
+  if constexpr (MA > 0) issue_meta(0);
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+    if (s < KT) issue(s, s);
+  wait_stage<LPS, S - 1>(min(S - 1, KT - 1));
+  __syncthreads();
+
+  bf16x8_t fx[2][TM];
+  raw_t fw[2][TN];
+  read_x(smem, 0, fx[0]);
+  read_w(smem, 0, fw[0]);
+  read_meta(0);
+  if constexpr (MA > 0)
+    if (KT > 4) issue_meta(1);
+  for (int kt0 = 0; kt0 < KT; kt0 += S) {
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const int kt = kt0 + u;
+      if (kt < KT) {
+        const uint8_t* st = smem + u * kStage;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          bf16x8_t w[TN];
+          if (Q != Quant::None && q == 3) {
+            // (this stage's scales are replaced below)
+#pragma unroll
+            for (int b = 0; b < TN; ++b) w[b] = weight(fw[1][b], b, 3);
+          }
+          if (q < 3) {
+            read_x(st, q + 1, fx[(q + 1) & 1]);
+            read_w(st, q + 1, fw[(q + 1) & 1]);
+          } else {
+            // (the last chunk's fragments are here in either branch: without
+            // this the products below would wait for the reads made in one)
+            wait_lgkmcnt0();
+          }
+          if (q == 3 && kt + 1 < KT) {
+            // stages kt + 2 .. kt + S - 1 may stay in flight
+            wait_stage<LPS, S - 2>(min(S - 2, KT - 2 - kt));
+            __syncthreads();  // stage kt + 1 visible; all of stage kt is in registers
+            const uint8_t* sn = smem + (u + 1 == S ? 0 : u + 1) * kStage;
+            read_x(sn, 0, fx[0]);
+            read_w(sn, 0, fw[0]);
+            read_meta(kt + 1);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int b = 0; b < TN; ++b) {
+            if (Q == Quant::None || q < 3) w[b] = weight(fw[q & 1][b], b, q);
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[b], fx[q & 1][a], acc[a][b], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          // the refills go out behind the matrix instructions: ahead of them,
+          // their issue kept them waiting after every barrier
+          if (q == 3) {
+            // (the first reader of block g, stage 4 g, waits after stages
+            // that are requested after it; block g - 2 was last read before
+            // the barrier above)
+            if constexpr (MA > 0)
+              if (((kt + 1) & 3) == 0 && kt + 5 < KT) issue_meta((kt + 5) >> 2);
+            if (kt + S < KT) issue(kt + S, u);
+          }
+        }
+      }
+    }
+  }
+
+  // Epilogue.  A wave's 32 x WN block goes through its own LDS region.
+  __syncthreads();
+  constexpr int PITCH = WN * 4 + 16;
+  constexpr int CPR = WN / 8;             // 8-column chunks per row
+  constexpr int ITERS = 32 * CPR / 64;
+  uint8_t* stg = smem + wave * (32 * PITCH);
+  const int cc = lane % CPR, n = n0 + wn * WN + cc * 8;
+  const bool col_ok = n < N;
+  const int nc = col_ok ? n : 0;
+  float bias[8], chs[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    bias[e] = p.epi != Epi::None ? p.bias[nc + e] : 0.0f;
+    chs[e] = Q == Quant::Int8 ? f16_bits_to_f32(reinterpret_cast<const uint16_t*>(p.scales)[nc + e]) : 1.0f;
+  }
+#pragma unroll
+  for (int a = 0; a < TM; ++a) {
+    const int mb = m0 + wm * WM + a * 32;
+    uint4 res[ITERS][2];
+    if (p.epi == Epi::BiasResidual) {
+#pragma unroll
+      for (int it = 0; it < ITERS; ++it) {
+        const size_t o = (size_t)min(mb + it * (64 / CPR) + lane / CPR, M - 1) * N + nc;
+        if (p.y_f32) {
+          res[it][0] = ldq(reinterpret_cast<const float*>(p.residual) + o);
+          res[it][1] = ldq(reinterpret_cast<const float*>(p.residual) + o + 4);
+        } else {
+          res[it][0] = ldq(reinterpret_cast<const bf16_t*>(p.residual) + o);
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < TN; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(stg + l32 * PITCH + (b * 32 + 8 * i + 4 * half) * 4) =
+            make_float4(acc[a][b][4 * i], acc[a][b][4 * i + 1], acc[a][b][4 * i + 2], acc[a][b][4 * i + 3]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      const int r = it * (64 / CPR) + lane / CPR, m = mb + r;
+      const float4 v0 = *reinterpret_cast<const float4*>(stg + r * PITCH + cc * 32);
+      const float4 v1 = *reinterpret_cast<const float4*>(stg + r * PITCH + cc * 32 + 16);
+      float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = (Q == Quant::Int8 ? v[e] * chs[e] : v[e]) + bias[e];
+      if (p.epi == Epi::BiasGelu) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = gelu_erf(v[e]);
+      } else if (p.epi == Epi::BiasResidual) {
+        const uint32_t w[8] = {res[it][0].x, res[it][0].y, res[it][0].z, res[it][0].w,
+                               res[it][1].x, res[it][1].y, res[it][1].z, res[it][1].w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          v[e] += __uint_as_float(p.y_f32 ? w[e] : (e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+      }
+      if (m < M && col_ok) {
+        const size_t o = (size_t)m * N + n;
+        if (p.y_f32) {
+          float4* y = reinterpret_cast<float4*>(reinterpret_cast<float*>(p.y) + o);
+          y[0] = make_float4(v[0], v[1], v[2], v[3]);
+          y[1] = make_float4(v[4], v[5], v[6], v[7]);
+        } else {
+          *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(p.y) + o) =
+              make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+template <int BM, int BN, int WMW, int WNW, int S, Quant Q>
+hipError_t launch_big_tile(const GemmParams& p, hipStream_t s) {
+  constexpr int lds = std::max(S * big_stage_bytes(BM, BN, Q) + 2 * big_meta_bytes(BN, Q), 8 * 32 * (BN / WNW * 4 + 16));
+  static_assert(lds <= 160 * 1024, "LDS of a workgroup");
+  static const hipError_t attr =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_big_kernel<BM, BN, WMW, WNW, S, Q>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (attr != hipSuccess) return attr;
+  const dim3 grid(((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN));
+  RLX_LOG_LAUNCH("gemm_big_kernel", grid, dim3(kBigThreads), lds, "tile=%dx%d stages=%d %s epi=%s M=%d N=%d K=%d", BM, BN,
+                 S, quant_name(Q), epi_name(p.epi), p.M, p.N, p.K);
+  hipLaunchKernelGGL((gemm_big_kernel<BM, BN, WMW, WNW, S, Q>), grid, dim3(kBigThreads), lds, s, p);
+  return hipGetLastError();
+}
+
+// One block per CU: a launch takes ceil(tiles / CUs) rounds, each of a time per
+// 64-k stage that was measured for each tile with all CUs busy (us, dense: 256 x
+// 256 1.84, 256 x 128 0.93, 128 x 128 0.58, 128 x 64 and 64 x 128 0.43).  The tile
+// with the least rounds x time is taken, the largest when equal.  Measured (us,
+// dense; 256 x 256 / 256 x 128 / 128 x 128 / 128 x 64): 2048 x 14336 x 4096 241 / 264 /
+// 274 / 379; 2048 x 4096 x 14336 330 / 208 / 260 / 356; 1024 x 4096 x 4096 - / 50 / 38
+// / 49; 509 x 4096 x 14336 305 / 171 / 125 / 97.
+enum BigTile { kBig256x256, kBig256x128, kBig128x128, kBigSmall };
+BigTile big_choice(const GemmParams& p, int small_m, int small_n) {
+  auto rounds = [&](int bm, int bn) {
+    const int64_t tiles = (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
+    return (int)((tiles + 255) / 256);
+  };
+  const int cost[4] = {184 * rounds(256, 256), 93 * rounds(256, 128), 58 * rounds(128, 128),
+                       43 * rounds(small_m, small_n)};
+  return static_cast<BigTile>(std::min_element(cost, cost + 4) - cost);
+}
+
+template <Quant Q>
+hipError_t launch_big_q(const GemmParams& p, hipStream_t s) {
+  if constexpr (Q == Quant::None) {
+    switch (big_choice(p, 128, 64)) {
+      case kBig256x256: return launch_big_tile<256, 256, 2, 4, 2, Q>(p, s);
+      case kBig256x128: return launch_big_tile<256, 128, 4, 2, 3, Q>(p, s);
+      case kBig128x128: return launch_big_tile<128, 128, 4, 2, 4, Q>(p, s);
+      default: return launch_big_tile<128, 64, 4, 2, 6, Q>(p, s);
+    }
+  } else {
+    // two rows of waves: each weight is converted by two of them
+    switch (big_choice(p, 64, 128)) {
+      case kBig256x256:
+      case kBig256x128: return launch_big_tile<256, 128, 2, 4, 3, Q>(p, s);
+      case kBig128x128: return launch_big_tile<128, 128, 2, 4, 4, Q>(p, s);
+      default: return launch_big_tile<64, 128, 2, 4, 4, Q>(p, s);
+    }
+  }
+}
+
+}  // namespace
+
+// Where one round of 64 x 64 tiles does and K is short, launches are a few
+// microseconds of fixed cost and the smaller kernels' two K groups per block
+// (dense 1500 x 384 x 1536: 10.0 against 11.9 us here) or cheaper conversion
+// (int4 min 333 x 1088 x 960: 11.9 against 13.2) win; the int4 and group-16
+// layouts only below K = 1024, where those kernels convert a weight once per
+// block (int4 1500 x 384 x 1536: 21.2 against 19.3).
+bool gemm_big_supported(const GemmParams& p) {
+  if (p.dtype != DType::BF16 || p.m_dev != nullptr || p.x_head_rows != 0 || p.x_stats || p.res_stats || p.y_stats ||
+      p.tile != 0 || p.N % 64 != 0 || p.K % 64 != 0 || p.K > (1 << 22))
+    return false;
+  const int64_t tiles64 = (int64_t)((p.M + 63) / 64) * (p.N / 64);
+  const bool long_conv = quant_int4(p.quant) || p.quant == Quant::Int8G16;
+  if (tiles64 <= 256 && p.K <= 2048 && !(long_conv && p.K >= 1024)) return false;
+  return true;
+}
+
+hipError_t launch_gemm_big(const GemmParams& p, hipStream_t s) {
+  switch (p.quant) {
+    case Quant::None: return launch_big_q<Quant::None>(p, s);
+    case Quant::Int8: return launch_big_q<Quant::Int8>(p, s);
+    case Quant::Int4: return launch_big_q<Quant::Int4>(p, s);
+    case Quant::Int8G: return launch_big_q<Quant::Int8G>(p, s);
+    case Quant::Int4M: return launch_big_q<Quant::Int4M>(p, s);
+    case Quant::Int8G16: return launch_big_q<Quant::Int8G16>(p, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace rlx

@@ -95,22 +95,6 @@ __device__ __forceinline__ void swap_lanes16(uint32_t& a, uint32_t& b) {
   b = r[1];
 }
 
-// Direct-to-LDS loads from a wave-uniform base and a lane's byte offset.
-__device__ __forceinline__ void lds_dma16_at(const uint8_t* base, uint32_t off, uint32_t lds_addr) {
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
-               : "memory", "m0");
-#pragma clang diagnostic pop
-}
-__device__ __forceinline__ void lds_dma4_at(const uint8_t* base, uint32_t off, uint32_t lds_addr) {
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_addr)
-               : "memory", "m0");
-#pragma clang diagnostic pop
-}
-
 // Eight int4 codes (k ascending, low nibble first) -> bf16 (128 + q), k
 // ascending.  A byte times 0x1001 holds its low nibble at bit 0 and its high
 // nibble at bit 16; one AND-OR keeps those and puts the exponent of 128 over

@@ -108,6 +108,11 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t s);
 bool gemv_supported(const GemmParams& p);
 hipError_t launch_gemv(const GemmParams& p, hipStream_t s);
 
+// Large-tile GEMM (gemm_big.hip): bf16 activations, dense or quantised weights.
+// launch_gemm takes it by itself where its rule says so.
+bool gemm_big_supported(const GemmParams& p);
+hipError_t launch_gemm_big(const GemmParams& p, hipStream_t s);
+
 // GGUF blocks (type 2 Q4_0, 3 Q4_1, 8 Q8_0) of an [N, K] tensor -> the Int4
 // (Q4_0, z = 8), Int4M (Q4_1) or Int8G (Q8_0) layout (gguf.hip).
 hipError_t launch_gguf_repack(const void* blocks, int type, int N, int K, void* codes, void* scales, void* zeros,

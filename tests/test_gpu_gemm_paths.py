@@ -322,3 +322,53 @@ def test_few_rows_infinite_and_huge_activations(rlx, scheme):
     if scheme != "int8":
         assert np.allclose(got[1], W.w[:, 40] * 2.0 ** 125, rtol=2.0 ** -20, atol=0)
     assert np.all(np.isfinite(got[2]))
+
+
+# The large-tile kernel's edges: one shape for each of its tiles (256 x 256,
+# 256 x 128, 128 x 128, 128 x 64 or 64 x 128) with ragged last rows and columns, K of
+# one stage, fewer stages than the ring, and across the 256-k scale blocks.
+BIG_SHAPES = [(4001, 4160, 64), (2000, 4032, 128), (1000, 4032, 192), (257, 4160, 576), (65, 4160, 1088),
+              (1100, 1088, 320)]
+
+
+@pytest.mark.parametrize("scheme", SCHEMES + ["dense"])
+@pytest.mark.parametrize("M,N,K", BIG_SHAPES)
+def test_large_tiles(rlx, scheme, M, N, K):
+    """fp32 sums of bf16 operands: the group schemes' weights rounded once to
+    bf16 (2^-9 relative), dense and int8 codes exact."""
+    rng = np.random.default_rng(300 + M + N + K)
+    x = to_bf16_exact(rng.normal(0, 1, (M, K)))
+    b = rng.normal(0, 0.5, N).astype(np.float32)
+    r = to_bf16_exact(rng.normal(0, 1, (M, N)))
+    if scheme == "dense":
+        w = to_bf16_exact(rng.normal(0, 0.05, (N, K)))
+        y = rlx.dequant_matmul(_dev(x, torch.bfloat16), _dev(w, torch.bfloat16), bias=_dev(b, torch.float32),
+                               residual=_dev(r, torch.bfloat16), epi=rlx.EPI_BIAS_RESIDUAL)
+    else:
+        W = Weights(scheme, N, K, seed=400 + M + N + K)
+        w = W.w
+        y = W.run(rlx, x, bias=b, residual=r, epi="residual")
+    got = y.float().cpu().numpy()
+    ref = oracle.linear(x, w, b) + r
+    tol = gemm_tolerance(x, w, ref, out_bf16=True, weight_rel=0.0 if scheme in ("dense", "int8") else 2.0 ** -9)
+    assert_within(got, ref, tol + 2.0 ** -24 * np.abs(ref) * 4, f"large tiles {scheme} {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("epi", EPIS)
+def test_large_tile_epilogues_f32_output(rlx, epi):
+    M, N, K = 600, 2112, 128
+    rng = np.random.default_rng(500 + len(epi))
+    x = to_bf16_exact(rng.normal(0, 1, (M, K)))
+    w = to_bf16_exact(rng.normal(0, 0.05, (N, K)))
+    b = rng.normal(0, 0.5, N).astype(np.float32)
+    r = rng.normal(0, 1, (M, N)).astype(np.float32)
+    y = rlx.dequant_matmul(_dev(x, torch.bfloat16), _dev(w, torch.bfloat16), bias=_dev(b, torch.float32),
+                           residual=_dev(r, torch.float32), epi=_epi_code(rlx, epi), out_dtype=torch.float32)
+    got = y.cpu().numpy()
+    ref = oracle.linear(x, w, None if epi == "none" else b)
+    pre = None
+    if epi == "gelu":
+        pre, ref = ref, oracle.gelu(ref)
+    if epi == "residual":
+        ref = ref + r
+    assert_within(got, ref, gemm_tolerance(x, w, ref, out_bf16=False, pre=pre) + 2.0 ** -24 * np.abs(ref) * 4, epi)
