@@ -125,37 +125,41 @@ __device__ __forceinline__ float2 row_ln_stats(const float2* part, int np, float
   load_ln_parts(part, np, v);
   return merge_ln_parts(v, np, eps);
 }
-// The same from statistics staged in LDS, for np parts known at compile
-// time (np even: rows of an even number of 64-column parts): the np / 2
-// 16-byte pairs are read at once (one LDS round trip), the sums are taken as
-// trees rather than one serial chain, and the reciprocal square root is the
-// hardware one (its argument is at least eps, never denormal).
-template <int NP>
-__device__ __forceinline__ float2 merge_ln_lds_n(const float2* part, float eps) {
-  static_assert(NP % 2 == 0 && NP >= 2 && NP <= kLnMaxParts, "even part count");
-  constexpr int NQ = NP / 2;
-  const float4* q = reinterpret_cast<const float4*>(part);
-  float4 v[NQ];
+// The same for NP parts known at compile time (NP even: rows of an even
+// number of 64-column parts), two a register quad: the sums are taken as trees
+// rather than one serial chain, and the reciprocal square root is the hardware
+// one (its argument is at least eps, never denormal).
+template <int NP, int NV>
+__device__ __forceinline__ float2 merge_ln_raw(const float4 (&v)[NV], float eps) {
+  static_assert(NV == NP / 2, "two parts a register quad");
+  float a[NV];
 #pragma unroll
-  for (int j = 0; j < NQ; ++j) v[j] = q[j];
-  float a[NQ];
+  for (int j = 0; j < NV; ++j) a[j] = v[j].x + v[j].z;
 #pragma unroll
-  for (int j = 0; j < NQ; ++j) a[j] = v[j].x + v[j].z;
+  for (int w = 1; w < NV; w *= 2)
 #pragma unroll
-  for (int w = 1; w < NQ; w *= 2)
-#pragma unroll
-    for (int j = 0; j + w < NQ; j += 2 * w) a[j] += a[j + w];
+    for (int j = 0; j + w < NV; j += 2 * w) a[j] += a[j + w];
   const float mean = a[0] * (1.0f / NP);
 #pragma unroll
-  for (int j = 0; j < NQ; ++j) {
+  for (int j = 0; j < NV; ++j) {
     const float d0 = v[j].x - mean, d1 = v[j].z - mean;
     a[j] = fmaf(64.0f * d0, d0, fmaf(64.0f * d1, d1, v[j].y + v[j].w));
   }
 #pragma unroll
-  for (int w = 1; w < NQ; w *= 2)
+  for (int w = 1; w < NV; w *= 2)
 #pragma unroll
-    for (int j = 0; j + w < NQ; j += 2 * w) a[j] += a[j + w];
+    for (int j = 0; j + w < NV; j += 2 * w) a[j] += a[j + w];
   return make_float2(mean, __builtin_amdgcn_rsqf(fmaf(a[0], 1.0f / (64.0f * NP), eps)));
+}
+// From statistics staged in LDS (one LDS round trip).
+template <int NP>
+__device__ __forceinline__ float2 merge_ln_lds_n(const float2* part, float eps) {
+  static_assert(NP % 2 == 0 && NP >= 2 && NP <= kLnMaxParts, "even part count");
+  const float4* q = reinterpret_cast<const float4*>(part);
+  float4 v[NP / 2];
+#pragma unroll
+  for (int j = 0; j < NP / 2; ++j) v[j] = q[j];
+  return merge_ln_raw<NP>(v, eps);
 }
 // Any part count: all kLnMaxParts entries are read at once (16-byte aligned,
 // 128 readable bytes: the caller pads) and the ones past np are masked.

@@ -1001,6 +1001,7 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t s) {
   if ((p.x_stats && !gemm_deferred_ln_supported(p.dtype, p.quant, p.K)) ||
       ((p.res_stats || p.y_stats) && !gemm_deferred_ln_supported(p.dtype, p.quant, p.N)))
     return hipErrorInvalidValue;
+  if (gemm_big_enc_supported(p)) return launch_gemm_big_enc(p, s);
   if (p.dtype == DType::F32) return launch_dense<float>(p, s);
   switch (p.quant) {
     case Quant::None: return launch_dense<bf16_t>(p, s);

@@ -77,8 +77,14 @@ __device__ __forceinline__ void big_tile(int bid, int m_tiles, int n_tiles, int&
   nt = r / rows;
 }
 
-template <int BM, int BN, int WMW, int WNW, int S, Quant Q>
+// ENC: the encoder's calls -- a device-side row count, activations that may be
+// head-major, and the deferred-LayerNorm roles of GemmParams (x_stats,
+// res_stats, y_stats), for rows of kBigParts * 64 columns where statistics are read.
+constexpr int kBigParts = 6;
+
+template <int BM, int BN, int WMW, int WNW, int S, Quant Q, bool ENC = false>
 __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
+  static_assert(!ENC || (Q == Quant::None && BN / WNW == 64), "a wave's columns are one statistics group");
   constexpr int NW = WMW * WNW;
   static_assert(NW * 64 == kBigThreads, "eight waves");
   constexpr int WM = BM / WMW, WN = BN / WNW;
@@ -97,8 +103,11 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
   static_assert(BM / 8 % NW == 0 && (WBT % NW == 0 || NW % WBT == 0) && (S - 1) * LPS < 64, "whole blocks, vmcnt range");
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
-  const int M = p.M, N = p.N, K = p.K;
+  const int N = p.N, K = p.K;
+  int M = p.M;
+  if constexpr (ENC) M = min(M, *p.m_dev);
   const int m_tiles = (M + BM - 1) / BM, n_tiles = (N + BN - 1) / BN;
+  if (ENC && (int)blockIdx.x >= m_tiles * n_tiles) return;
   int mt, nt;
   big_tile(blockIdx.x, m_tiles, n_tiles, mt, nt);
   const int m0 = mt * BM, n0 = nt * BN;
@@ -107,16 +116,34 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
   const int l32 = lane & 31, half = lane >> 5;
   const int KT = K / 64;
 
+  // The rows' LayerNorm statistics, one row a thread (the first BM threads x,
+  // the last BM the residual), in registers until the epilogue; requested
+  // before the operands, whose waits then cover them.
+  float4 st_raw[ENC ? kBigParts / 2 : 1];
+  if constexpr (ENC) {
+    static_assert(2 * BM <= kBigThreads, "one row a thread");
+    const float2* src = tid < BM ? p.x_stats : tid >= kBigThreads - BM ? p.res_stats : nullptr;
+    const int row = min(m0 + (tid < BM ? tid : tid - (kBigThreads - BM)), M - 1);
+#pragma unroll
+    for (int j = 0; j < kBigParts / 2; ++j)
+      st_raw[j] = src ? reinterpret_cast<const float4*>(src + (size_t)row * kBigParts)[j] : make_float4(0, 0, 0, 0);
+  }
+
   // Lane offsets of the loads from wave-uniform bases; rows past M or N repeat
-  // the last row (nothing is stored for them).
-  const uint32_t xpitch = K * 2, wpitch = K / 64 * WB;
+  // the last row (nothing is stored for them).  Head-major activations
+  // ([K/32][x_head_rows][32], as the fused attention writes them): a stage
+  // spans two heads, its chunk c in head c / 4.
+  const bool hm = ENC && p.x_head_rows > 0;
+  const uint32_t xpitch = hm ? 64 : K * 2, wpitch = K / 64 * WB;
+  const size_t xstage = hm ? (size_t)p.x_head_rows * 128 : 128;
   const uint8_t* xbase = reinterpret_cast<const uint8_t*>(p.x) + (size_t)m0 * xpitch;
   const uint8_t* wbase = reinterpret_cast<const uint8_t*>(p.w) + (size_t)n0 * wpitch;
   uint32_t xo[XI], wo[WI];
 #pragma unroll
   for (int i = 0; i < XI; ++i) {
     const int row = 8 * (wave + i * NW) + (lane >> 3);
-    xo[i] = min(row, M - 1 - m0) * xpitch + big_swz(row, lane & 7) * 16;
+    const int c = big_swz(row, lane & 7);
+    xo[i] = min(row, M - 1 - m0) * xpitch + (hm ? (c >> 2) * p.x_head_rows * 64 + (c & 3) * 16 : c * 16);
   }
 #pragma unroll
   for (int i = 0; i < WI; ++i) {
@@ -144,7 +171,7 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
     const uint32_t base = lds0 + slot * kStage;
 #pragma unroll
     for (int i = 0; i < XI; ++i)
-      lds_dma16_at(xbase + (size_t)kt * 128, xo[i], __builtin_amdgcn_readfirstlane(base + (wave + i * NW) * 1024));
+      lds_dma16_at(xbase + kt * xstage, xo[i], __builtin_amdgcn_readfirstlane(base + (wave + i * NW) * 1024));
 #pragma unroll
     for (int i = 0; i < WI; ++i)
       lds_dma16_at(wbase + (size_t)kt * WB, wo[i], __builtin_amdgcn_readfirstlane(base + BM * 128 + (wave + i * NW) % WBT * 1024));
@@ -278,20 +305,38 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
     }
   }
 
-  // Epilogue.  A wave's 32 x WN block goes through its own LDS region.
+  // Epilogue.  A wave's 32 x WN block goes through its own LDS region; the rows'
+  // merged statistics (x, then residual) lie behind the eight regions.
   __syncthreads();
   constexpr int PITCH = WN * 4 + 16;
   constexpr int CPR = WN / 8;             // 8-column chunks per row
   constexpr int ITERS = 32 * CPR / 64;
   uint8_t* stg = smem + wave * (32 * PITCH);
+  float2* mrg = reinterpret_cast<float2*>(smem + 8 * 32 * PITCH);
+  if constexpr (ENC) {
+    if (p.x_stats || p.res_stats) {
+      if (tid < BM || tid >= kBigThreads - BM)
+        mrg[tid < BM ? tid : tid - (kBigThreads - BM) + BM] = merge_ln_raw<kBigParts>(st_raw, p.ln_eps);
+      __syncthreads();
+    }
+  }
   const int cc = lane % CPR, n = n0 + wn * WN + cc * 8;
   const bool col_ok = n < N;
   const int nc = col_ok ? n : 0;
-  float bias[8], chs[8];
+  // per-column operands: bias, int8 scales; fold_u or the residual's gamma and beta
+  float bias[8], chs[8], cg[8], cb[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     bias[e] = p.epi != Epi::None ? p.bias[nc + e] : 0.0f;
     chs[e] = Q == Quant::Int8 ? f16_bits_to_f32(reinterpret_cast<const uint16_t*>(p.scales)[nc + e]) : 1.0f;
+    cg[e] = cb[e] = 0.0f;
+    if constexpr (ENC) {
+      if (p.x_stats) cg[e] = p.fold_u[nc + e];
+      if (p.res_stats) {
+        cg[e] = p.res_gamma[nc + e];
+        cb[e] = p.res_beta[nc + e];
+      }
+    }
   }
 #pragma unroll
   for (int a = 0; a < TM; ++a) {
@@ -322,6 +367,13 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
       const float4 v0 = *reinterpret_cast<const float4*>(stg + r * PITCH + cc * 32);
       const float4 v1 = *reinterpret_cast<const float4*>(stg + r * PITCH + cc * 32 + 16);
       float v[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+      if constexpr (ENC) {
+        if (p.x_stats) {  // rstd (acc - mean u) + folded bias
+          const float2 st = mrg[wm * WM + a * 32 + r];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = st.y * fmaf(-st.x, cg[e], v[e]);
+        }
+      }
 #pragma unroll
       for (int e = 0; e < 8; ++e) v[e] = (Q == Quant::Int8 ? v[e] * chs[e] : v[e]) + bias[e];
       if (p.epi == Epi::BiasGelu) {
@@ -330,9 +382,42 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
       } else if (p.epi == Epi::BiasResidual) {
         const uint32_t w[8] = {res[it][0].x, res[it][0].y, res[it][0].z, res[it][0].w,
                                res[it][1].x, res[it][1].y, res[it][1].z, res[it][1].w};
+        float rr[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          v[e] += __uint_as_float(p.y_f32 ? w[e] : (e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+          rr[e] = __uint_as_float(p.y_f32 ? w[e] : (e & 1) ? w[e >> 1] & 0xffff0000u : w[e >> 1] << 16);
+        if constexpr (ENC) {
+          if (p.res_stats) {
+            const float2 st = mrg[BM + wm * WM + a * 32 + r];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rr[e] = fmaf((rr[e] - st.x) * st.y, cg[e], cb[e]);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] += rr[e];
+      }
+      const uint4 o4 = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]),
+                                  pack_bf16x2(v[6], v[7]));
+      if constexpr (ENC) {
+        if (p.y_stats) {
+          // statistics of the stored (rounded) values over this wave's 64
+          // columns: lanes 8j .. 8j + 7 hold a row's consecutive chunks
+          const uint32_t wv[4] = {o4.x, o4.y, o4.z, o4.w};
+          float f[8], sum = 0.0f;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            f[2 * e] = __uint_as_float(wv[e] << 16);
+            f[2 * e + 1] = __uint_as_float(wv[e] & 0xffff0000u);
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) sum += f[e];
+          const float mean = dpp_sum8(sum) * (1.0f / 64.0f);
+          float m2 = 0.0f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) m2 = fmaf(f[e] - mean, f[e] - mean, m2);
+          m2 = dpp_sum8(m2);
+          if (cc == 0 && m < M && col_ok) p.y_stats[(size_t)m * (N >> 6) + (n >> 6)] = make_float2(mean, m2);
+        }
       }
       if (m < M && col_ok) {
         const size_t o = (size_t)m * N + n;
@@ -341,8 +426,7 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
           y[0] = make_float4(v[0], v[1], v[2], v[3]);
           y[1] = make_float4(v[4], v[5], v[6], v[7]);
         } else {
-          *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(p.y) + o) =
-              make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+          *reinterpret_cast<uint4*>(reinterpret_cast<bf16_t*>(p.y) + o) = o4;
         }
       }
     }
@@ -350,18 +434,19 @@ __global__ __launch_bounds__(kBigThreads) void gemm_big_kernel(GemmParams p) {
   }
 }
 
-template <int BM, int BN, int WMW, int WNW, int S, Quant Q>
+template <int BM, int BN, int WMW, int WNW, int S, Quant Q, bool ENC = false>
 hipError_t launch_big_tile(const GemmParams& p, hipStream_t s) {
-  constexpr int lds = std::max(S * big_stage_bytes(BM, BN, Q) + 2 * big_meta_bytes(BN, Q), 8 * 32 * (BN / WNW * 4 + 16));
+  constexpr int lds = std::max(S * big_stage_bytes(BM, BN, Q) + 2 * big_meta_bytes(BN, Q),
+                               8 * 32 * (BN / WNW * 4 + 16) + (ENC ? 2 * BM * 8 : 0));
   static_assert(lds <= 160 * 1024, "LDS of a workgroup");
   static const hipError_t attr =
-      hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_big_kernel<BM, BN, WMW, WNW, S, Q>),
+      hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_big_kernel<BM, BN, WMW, WNW, S, Q, ENC>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (attr != hipSuccess) return attr;
   const dim3 grid(((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN));
   RLX_LOG_LAUNCH("gemm_big_kernel", grid, dim3(kBigThreads), lds, "tile=%dx%d stages=%d %s epi=%s M=%d N=%d K=%d", BM, BN,
                  S, quant_name(Q), epi_name(p.epi), p.M, p.N, p.K);
-  hipLaunchKernelGGL((gemm_big_kernel<BM, BN, WMW, WNW, S, Q>), grid, dim3(kBigThreads), lds, s, p);
+  hipLaunchKernelGGL((gemm_big_kernel<BM, BN, WMW, WNW, S, Q, ENC>), grid, dim3(kBigThreads), lds, s, p);
   return hipGetLastError();
 }
 
@@ -419,6 +504,27 @@ bool gemm_big_supported(const GemmParams& p) {
   const bool long_conv = quant_int4(p.quant) || p.quant == Quant::Int8G16;
   if (tiles64 <= 256 && p.K <= 2048 && !(long_conv && p.K >= 1024)) return false;
   return true;
+}
+
+// The encoder's narrow projections (output projection and FFN-down, N = hidden)
+// from 16384 padded rows up: 128 x 128 tiles with two stages, two blocks per CU.
+// The host knows only the padded row count; of the tiles measured, these are at
+// or near the best whether half or all of the rows are real (us per forward,
+// 64-row tiles or four-wave 128 x 128 / 256 x 128 / 128 x 128 four stages / these):
+// batch 128 x 128 half full 544 / 574 / 498 / 536, full 828 / 668 / 754 / 685; batch 256
+// half full 987 / 830 / 899 / 844, full 1387 / 1270 / 1268 / 1284; 64 x 512 1657 / 1533 /
+// 1521 / 1481.  Below 16384 rows 64 x 64 tiles fill the CUs better (batch 64: 326
+// against 419).  The wide projections (N >= 1024) stay with the four-wave kernels,
+// whose two blocks per CU overlap one's GELU with the other's loads (batch 256:
+// 830 against 854 with these tiles for them).
+bool gemm_big_enc_supported(const GemmParams& p) {
+  return p.dtype == DType::BF16 && p.quant == Quant::None && p.m_dev != nullptr && p.M >= 16384 && p.N < 1024 &&
+         p.N % 128 == 0 && p.K % 64 == 0 && p.K <= (1 << 22) && !p.y_f32 && p.tile == 0 && !p.y_gamma && !p.res_scaled &&
+         (!p.x_stats || p.K == 64 * kBigParts) && (!p.res_stats || p.N == 64 * kBigParts) && !(p.x_stats && p.res_stats);
+}
+
+hipError_t launch_gemm_big_enc(const GemmParams& p, hipStream_t s) {
+  return launch_big_tile<128, 128, 4, 2, 2, Quant::None, true>(p, s);
 }
 
 hipError_t launch_gemm_big(const GemmParams& p, hipStream_t s) {

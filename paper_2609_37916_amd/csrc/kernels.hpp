@@ -112,6 +112,9 @@ hipError_t launch_gemv(const GemmParams& p, hipStream_t s);
 // launch_gemm takes it by itself where its rule says so.
 bool gemm_big_supported(const GemmParams& p);
 hipError_t launch_gemm_big(const GemmParams& p, hipStream_t s);
+// The same for the encoder's dense calls (device-side row count, deferred LayerNorm).
+bool gemm_big_enc_supported(const GemmParams& p);
+hipError_t launch_gemm_big_enc(const GemmParams& p, hipStream_t s);
 
 // GGUF blocks (type 2 Q4_0, 3 Q4_1, 8 Q8_0) of an [N, K] tensor -> the Int4
 // (Q4_0, z = 8), Int4M (Q4_1) or Int8G (Q8_0) layout (gguf.hip).
