@@ -52,7 +52,7 @@ KERNEL_SOURCES = {
     "gemv": ("gemv.hip",),
     "encoder_pipe": ("pipe.hip", "gemm_tile.hpp", "qkv_attention.hpp"),
     # every kernel of an encoder forward (the counter summaries of a whole forward)
-    "encoder": ("attention.hip", "qkv_attention.hpp", "gemm.hip", "gemm_big.hip", "gemm_tile.hpp", "rowops.hip", "pipe.hip"),
+    "encoder": ("attention.hip", "qkv_attention.hpp", "gemm.hip", "gemm_big.hip", "gemm_f32.hip", "gemm_tile.hpp", "rowops.hip", "pipe.hip"),
 }
 
 

@@ -129,7 +129,9 @@ rlx_status rlx_masked_attention(const void* q, const void* k, const void* v, int
  * x: [M,K] row-major, dtype x_dt (RLX_BF16 or RLX_F32; quantised schemes
  * need RLX_BF16).  W: [N,K] in the layout of `scheme` (nn.Linear
  * convention: one row per output feature).  bias: f32 [N] (needed by every
- * epilogue except RLX_EPI_NONE).  y: [M,N] of dtype y_dt: RLX_BF16 or
+ * epilogue except RLX_EPI_NONE).  f32 operands are multiplied as sums of three
+ * bf16 numbers each (exact), six products of parts with fp32 accumulation: at
+ * least the accuracy of an fp32 product.  y: [M,N] of dtype y_dt: RLX_BF16 or
  * RLX_F32 for bf16 x, RLX_F32 for f32 x.  residual: [M,N] of dtype y_dt
  * (only for RLX_EPI_BIAS_RESIDUAL).  Accumulation is fp32; bf16 outputs are
  * rounded once at the end, f32 outputs are the fp32 result of the epilogue.
@@ -314,6 +316,9 @@ typedef struct rlx_encoder rlx_encoder;
  * 1.. with the preceding LayerNorm's gamma folded in, and folded biases from
  * beta, bqkv and b1; later changes to those arrays, the LayerNorm parameters
  * or bqkv/b1 are not seen by the handle.
+ * With f32 the handle holds every matrix a second time, split into three bf16
+ * parts whose sum it is (6 bytes a weight), for the bf16 matrix cores: create
+ * reads the matrices, and later changes to them are not seen.
  * With quantised weights (bf16 activations) and pooled output, the handle
  * also holds bf16 copies of every layer's matrices (Section VI's
  * DequantMatMul, taken once per forward): the first kernel of each forward

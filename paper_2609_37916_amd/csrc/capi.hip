@@ -198,6 +198,12 @@ struct rlx_encoder {
   };
   std::vector<Folded> folded;
   void* fold_mem = nullptr;
+  // f32: every layer's matrices split into three bf16 parts, once, at create.
+  struct SplitW {
+    const void *wqkv, *wo, *w1, *w2;
+  };
+  std::vector<SplitW> split;
+  void* split_mem = nullptr;
   // Quantised weights, calls of at least dq_min_tokens = B*S positions: one
   // kernel at the start of the forward dequantises every layer to bf16
   // (gamma folded in where the dense deferred LayerNorm wants it) and the
@@ -259,6 +265,7 @@ struct FwdCtx {
   const DequantJob* dq_jobs;
   int dq_njobs, dq_max_elems;
   int2* rank_rows = nullptr;  // [B]: (first row, real tokens) by launch rank, beside the order
+  const rlx_encoder::SplitW* split = nullptr;  // f32 handles
 };
 
 // The forward of B sequences of S positions: with the dequantisation prologue
@@ -269,7 +276,7 @@ FwdCtx ctx_of(const rlx_encoder* e, int B, int S) {
                 e->tok_src, e->tok_dst, e->order, e->X, e->X1, e->A, e->CTX, e->QKV, e->G, e->deferred, e->S1,
                 e->S2, dq ? e->dq_folded.data() : e->folded.data(), e->pipe ? e->pipe_grid : 0, e->pipe_layers,
                 e->pipe_sync, dq ? e->dq_jobs : nullptr, dq ? e->dq_njobs : 0, dq ? e->dq_max_elems : 0,
-                e->rank_rows};
+                e->rank_rows, e->split.empty() ? nullptr : e->split.data()};
 }
 
 // Workspace layout for max_batch sequences of max_seq tokens (256-byte aligned regions).
@@ -457,6 +464,7 @@ rlx_status enqueue_forward(const FwdCtx& fc, const void* input, const uint8_t* m
       g.x = E.X; g.w = wqkv; g.scales = L.wqkv_scales; g.zeros = L.wqkv_zeros; g.bias = bqkv;
       g.residual = nullptr; g.y = E.QKV; g.N = 3 * H; g.K = H; g.epi = Epi::Bias;
       g.x_stats = x_def ? E.S2 : nullptr; g.fold_u = uqkv;
+      g.w_split = E.split ? E.split[l].wqkv : nullptr;
       STEP(K_GEMM_QKV, launch_gemm(g, ss));
       g.x_stats = nullptr; g.fold_u = nullptr;
 
@@ -482,6 +490,7 @@ rlx_status enqueue_forward(const FwdCtx& fc, const void* input, const uint8_t* m
     }
     g.y_stats = E.deferred ? E.S1 : nullptr;
     g.y_gamma = gsc ? L.ln1_gamma : nullptr;
+    g.w_split = E.split ? E.split[l].wo : nullptr;
     STEP(K_GEMM_ATTN_OUT, launch_gemm(g, ss));
     g.x_head_rows = 0;
     g.res_stats = nullptr; g.res_gamma = g.res_beta = nullptr; g.y_stats = nullptr;
@@ -514,10 +523,12 @@ rlx_status enqueue_forward(const FwdCtx& fc, const void* input, const uint8_t* m
     STEP(K_LN1, launch_layer_norm(E.A, L.ln1_gamma, L.ln1_beta, c.ln_eps, H, n_dev, T, E.X1, E.dt, ss));
     g.x = E.X1; g.w = L.w1; g.scales = L.w1_scales; g.zeros = L.w1_zeros; g.bias = L.b1;
     g.residual = nullptr; g.y = E.G; g.N = F; g.K = H; g.epi = Epi::BiasGelu;
+    g.w_split = E.split ? E.split[l].w1 : nullptr;
     STEP(K_GEMM_FFN_UP, launch_gemm(g, ss));
 
     g.x = E.G; g.w = L.w2; g.scales = L.w2_scales; g.zeros = L.w2_zeros; g.bias = L.b2;
     g.residual = E.X1; g.y = E.A; g.N = H; g.K = F; g.epi = Epi::BiasResidual;
+    g.w_split = E.split ? E.split[l].w2 : nullptr;
     STEP(K_GEMM_FFN_DOWN, launch_gemm(g, ss));
     STEP(K_LN2, launch_layer_norm(E.A, L.ln2_gamma, L.ln2_beta, c.ln_eps, H, n_dev, T, E.X, E.dt, ss));
   }
@@ -735,6 +746,38 @@ rlx_status fold_layer_norms(rlx_encoder* e) {
     }
   }
   RLX_HIP(hipStreamSynchronize(e->cap_stream), "encoder_create: fold LayerNorms");
+  return RLX_OK;
+}
+
+// f32 handles: the bf16 parts of every layer's matrices (gemm_f32.hip), made on
+// the capture stream, and waited for.
+rlx_status split_f32_weights(rlx_encoder* e) {
+  const rlx_encoder_config& c = e->cfg;
+  if (e->dt != DType::F32) return RLX_OK;
+  const size_t H = c.hidden, F = c.ffn, part = 6;  // bytes a weight
+  const size_t layer = align_up(3 * H * H * part, 256) + align_up(H * H * part, 256) + 2 * align_up(F * H * part, 256);
+  hipError_t he = hipMalloc(&e->split_mem, layer * c.layers);
+  if (he != hipSuccess) {
+    e->split_mem = nullptr;
+    return fail(RLX_ERR_OOM, "encoder_create: split weights of %zu bytes: %s", layer * c.layers, hipGetErrorString(he));
+  }
+  uint8_t* at = static_cast<uint8_t*>(e->split_mem);
+  for (int l = 0; l < c.layers; ++l) {
+    const rlx_layer_weights& L = e->layers[l];
+    auto split = [&](const void* w, int N, int K, const void** out) {
+      *out = at;
+      hipError_t r = launch_split_weights(w, N, K, at, e->cap_stream);
+      at += align_up((size_t)N * K * part, 256);
+      return r;
+    };
+    rlx_encoder::SplitW s{};
+    RLX_HIP(split(L.wqkv, 3 * c.hidden, c.hidden, &s.wqkv), "encoder_create: split Wqkv");
+    RLX_HIP(split(L.wo, c.hidden, c.hidden, &s.wo), "encoder_create: split Wo");
+    RLX_HIP(split(L.w1, c.ffn, c.hidden, &s.w1), "encoder_create: split W1");
+    RLX_HIP(split(L.w2, c.hidden, c.ffn, &s.w2), "encoder_create: split W2");
+    e->split.push_back(s);
+  }
+  RLX_HIP(hipStreamSynchronize(e->cap_stream), "encoder_create: split weights");
   return RLX_OK;
 }
 
@@ -1105,6 +1148,11 @@ rlx_status rlx_encoder_create(const rlx_encoder_config* cfg, const rlx_encoder_w
     rlx_encoder_destroy(e);
     return hip_fail(he, "encoder_create: stream and event");
   }
+  st = split_f32_weights(e);
+  if (st != RLX_OK) {
+    rlx_encoder_destroy(e);
+    return st;
+  }
   if (e->deferred) {
     st = fold_layer_norms(e);
     if (st == RLX_OK) st = setup_dequant_prologue(e);
@@ -1209,6 +1257,7 @@ void rlx_encoder_destroy(rlx_encoder* e) {
   if (e->ws) (void)hipFree(e->ws);
   if (e->fold_mem) (void)hipFree(e->fold_mem);
   if (e->dq_mem) (void)hipFree(e->dq_mem);
+  if (e->split_mem) (void)hipFree(e->split_mem);
   if (e->pipe_mem) (void)hipFree(e->pipe_mem);
   delete e;
 }

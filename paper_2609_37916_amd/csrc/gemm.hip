@@ -738,26 +738,31 @@ hipError_t launch_dma_tile(const GemmParams& p, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_dense(const GemmParams& p, hipStream_t s) {
-  int tile = p.tile;
-  if (tile == kTileAuto) {
-    // measured at the encoder's shapes (2-4 k tokens): 64x64 for N = 384, 64x128
-    // for the wide projections; 128x128 only pays off from ~16 k rows up
-    if (p.N % 128 == 0 && p.M >= 16384) tile = kTile128x128;
-    else if (p.N % 128 == 0 && p.N >= 1024) tile = kTile64x128;
-    else tile = kTile64x64;
-  }
-  if (p.N % 128 != 0 && (tile == kTile128x128 || tile == kTile64x128)) tile = kTile64x64;
-  switch (tile) {
-    // stage counts keep these configurations within 80 KB of LDS: two blocks per CU
-    case kTile128x128: return launch_dma_tile<128, 128, 2, T>(p, s);
-    case kTile64x128: return launch_dma_tile<64, 128, 3, T>(p, s);
-    case kTile128x64: return launch_dma_tile<128, 64, 3, T>(p, s);
-    // 64 x 64: one block per CU at the encoder's N = 384 shapes, so bf16 splits
-    // each stage's K between two groups of four waves (eight waves per CU), and
-    // the ring is four stages deep: in the forward the operands come from the
-    // last-level cache or HBM, not L2, and three stages in flight measured
-    // 8 us per forward faster than two
-    default: return launch_dma_tile<64, 64, 4, T, sizeof(T) == 2 ? 2 : 1>(p, s);
+  // (f32: only rows too long for gemm_f32.hip's offsets)
+  if constexpr (sizeof(T) == 4) {
+    return launch_dma_tile<64, 64, 4, T>(p, s);
+  } else {
+    int tile = p.tile;
+    if (tile == kTileAuto) {
+      // measured at the encoder's shapes (2-4 k tokens): 64x64 for N = 384, 64x128
+      // for the wide projections; 128x128 only pays off from ~16 k rows up
+      if (p.N % 128 == 0 && p.M >= 16384) tile = kTile128x128;
+      else if (p.N % 128 == 0 && p.N >= 1024) tile = kTile64x128;
+      else tile = kTile64x64;
+    }
+    if (p.N % 128 != 0 && (tile == kTile128x128 || tile == kTile64x128)) tile = kTile64x64;
+    switch (tile) {
+      // stage counts keep these configurations within 80 KB of LDS: two blocks per CU
+      case kTile128x128: return launch_dma_tile<128, 128, 2, T>(p, s);
+      case kTile64x128: return launch_dma_tile<64, 128, 3, T>(p, s);
+      case kTile128x64: return launch_dma_tile<128, 64, 3, T>(p, s);
+      // 64 x 64: one block per CU at the encoder's N = 384 shapes, so bf16 splits
+      // each stage's K between two groups of four waves (eight waves per CU), and
+      // the ring is four stages deep: in the forward the operands come from the
+      // last-level cache or HBM, not L2, and three stages in flight measured
+      // 8 us per forward faster than two
+      default: return launch_dma_tile<64, 64, 4, T, 2>(p, s);
+    }
   }
 }
 
@@ -1002,6 +1007,7 @@ hipError_t launch_gemm(const GemmParams& p, hipStream_t s) {
       ((p.res_stats || p.y_stats) && !gemm_deferred_ln_supported(p.dtype, p.quant, p.N)))
     return hipErrorInvalidValue;
   if (gemm_big_enc_supported(p)) return launch_gemm_big_enc(p, s);
+  if (gemm_f32_supported(p)) return launch_gemm_f32(p, s);
   if (p.dtype == DType::F32) return launch_dense<float>(p, s);
   switch (p.quant) {
     case Quant::None: return launch_dense<bf16_t>(p, s);

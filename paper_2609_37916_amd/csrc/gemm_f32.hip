@@ -1,0 +1,347 @@
+// fp32 GEMM on the bf16 matrix cores, with fused epilogues:
+//   y[m,n] = epi( sum_k x[m,k] W[n,k] ),  x, W, y f32 (Linear block, Section III-A).
+//
+// The fp32 matrix instructions bound the fp32 path (157 TFLOP/s against 2.5
+// PFLOP/s in bf16).  A float is exactly the sum of three bf16 numbers:
+// h = bf16(a), m = bf16(a - h), l = a - h - m (round to nearest: |a - h| <=
+// 2^-9 |a|, |l| <= 2^-18 |a|, and what is left of 24 bits after two roundings of
+// 8 fits the third).  Of the nine products of two such sums the six of weight
+// 2^-18 and above are taken, h h, h m, m h, h l, l h, m m; the others are below
+// 2^-26 of |a b| each.  The matrix cores add exact products of bf16 in fp32, so
+// the result differs from the exact sum by fp32 accumulation like that of the
+// fp32 instructions, with fewer roundings per k (6 instructions per 16 k
+// against 8); errors and times stand at launch_gemm_f32.  What bounds the kernel
+// is the operand stream (batch 64 FFN-up: 392 MB of stages in 40 us, about 17
+// bytes per clock and CU) and the vector work of splitting, then the matrix
+// instructions.
+// An output that is not finite (an infinity in the operands, or a value that
+// rounds past the bf16 range) is computed again term by term in fp32.
+//
+//  * Operands come as in the large-tile bf16 kernel: direct-to-LDS stages (32 k,
+//    128-byte rows, swizzled) in a ring of S; a 16-k chunk's floats are read
+//    into registers, split there, and multiplied while the next chunk is split.
+//  * A wave's 64 x 64 block (32 x 32 accumulators) needs 24 matrix instructions
+//    of 32 cycles per chunk against ~176 vector instructions of 4 cycles for
+//    the splitting, half of it for weights that come split (an encoder's, split
+//    once at create); the scheduling hints interleave the two.
+#include <algorithm>
+
+#include "common.hpp"
+#include "kernels.hpp"
+
+namespace rlx {
+namespace {
+
+__device__ __forceinline__ uint4 ldf(const void* p) { return *reinterpret_cast<const uint4*>(p); }
+__device__ __forceinline__ int f_swz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+
+// Eight floats -> three bf16 operands.
+struct Split {
+  bf16x8_t h, m, l;
+};
+__device__ __forceinline__ Split split3(uint4 u0, uint4 u1) {
+  const uint32_t u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+  uint32_t h[4], m[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float a = __uint_as_float(u[2 * i]), b = __uint_as_float(u[2 * i + 1]);
+    h[i] = pack_bf16x2(a, b);
+    const float ra = a - __uint_as_float(h[i] << 16), rb = b - __uint_as_float(h[i] & 0xffff0000u);
+    m[i] = pack_bf16x2(ra, rb);
+    l[i] = pack_bf16x2(ra - __uint_as_float(m[i] << 16), rb - __uint_as_float(m[i] & 0xffff0000u));
+  }
+  return Split{as_bf16x8(make_uint4(h[0], h[1], h[2], h[3])), as_bf16x8(make_uint4(m[0], m[1], m[2], m[3])),
+               as_bf16x8(make_uint4(l[0], l[1], l[2], l[3]))};
+}
+
+// Weights split once: per row and 32 k, 32 bf16 of h, then of m, then of l.
+__global__ __launch_bounds__(256) void split_weights_kernel(const float* w, int64_t n32, uint16_t* out) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // eight floats each
+  if (i >= n32 * 4) return;
+  const Split v = split3(ldf(w + i * 8), ldf(w + i * 8 + 4));
+  uint16_t* o = out + (i >> 2) * 96 + (i & 3) * 8;
+  *reinterpret_cast<uint4*>(o) = __builtin_bit_cast(uint4, v.h);
+  *reinterpret_cast<uint4*>(o + 32) = __builtin_bit_cast(uint4, v.m);
+  *reinterpret_cast<uint4*>(o + 64) = __builtin_bit_cast(uint4, v.l);
+}
+
+// WMW x WNW waves of BM/WMW x BN/WNW outputs.  WP: the weights come split
+// (p.w_split): no vector work for them, 192 bytes a row and stage.
+template <int BM, int BN, int WMW, int WNW, int S, bool WP>
+__global__ __launch_bounds__(WMW * WNW * 64) void gemm_f32_kernel(GemmParams p) {
+  constexpr int NW = WMW * WNW;
+  constexpr int WM = BM / WMW, WN = BN / WNW;
+  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int WB = WP ? 192 : 128;  // weight bytes of a row per stage
+  constexpr int kStage = BM * 128 + BN * WB;
+  constexpr int XI = BM / 8 / NW, WI = BN * WB / 1024 / NW;  // 1 KB blocks per wave and stage
+  constexpr int LPS = XI + WI;
+  static_assert(BM / 8 % NW == 0 && BN * WB / 1024 % NW == 0 && (S - 1) * LPS < 64, "whole blocks, vmcnt range");
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+
+  const int N = p.N, K = p.K;
+  int M = p.M;
+  if (p.m_dev) M = min(M, *p.m_dev);
+  const int m_tiles = (M + BM - 1) / BM, n_tiles = (N + BN - 1) / BN;
+  const int total = m_tiles * n_tiles;
+  if ((int)blockIdx.x >= total) return;
+  // XCD bid % 8 takes a contiguous run of tiles, down a band of four row tiles
+  // first, so that its tiles share operand rows through its L2
+  const int q8 = total >> 3, r8 = total & 7, xcd = blockIdx.x & 7;
+  const int t = xcd * q8 + min(xcd, r8) + ((int)blockIdx.x >> 3);
+  const int band = t / (4 * n_tiles), rem = t - band * 4 * n_tiles, rows = min(4, m_tiles - band * 4);
+  const int m0 = (band * 4 + rem % rows) * BM, n0 = rem / rows * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WNW, wn = wave % WNW;
+  const int l32 = lane & 31, half = lane >> 5;
+  const int KT = K / 32;
+
+  const uint32_t pitch = K * 4;
+  const uint8_t* xbase = reinterpret_cast<const uint8_t*>(p.x) + (size_t)m0 * pitch;
+  const uint32_t wpitch = K / 32 * WB;
+  const uint8_t* wbase = reinterpret_cast<const uint8_t*>(WP ? p.w_split : p.w) + (size_t)n0 * wpitch;
+  uint32_t xo[XI], wo[WI];
+#pragma unroll
+  for (int i = 0; i < XI; ++i) {
+    const int row = 8 * (wave + i * NW) + (lane >> 3);
+    xo[i] = min(row, M - 1 - m0) * pitch + f_swz(row, lane & 7) * 16;
+  }
+#pragma unroll
+  for (int i = 0; i < WI; ++i) {
+    // split rows: the four chunks of a part permuted by (row / 4) mod 4, which
+    // spreads a quarter wave's reads (16 rows of 48 banks) over all banks
+    const int b = (wave + i * NW) * 1024 + lane * 16, row = b / WB, ch = b % WB / 16;
+    wo[i] = min(row, N - 1 - n0) * wpitch + (WP ? ch ^ ((row >> 2) & 3) : f_swz(row, ch)) * 16;
+  }
+  const uint32_t lds0 = lds_addr_of(smem);
+  auto issue = [&](int kt, int slot) {
+    const uint32_t base = lds0 + slot * kStage;
+#pragma unroll
+    for (int i = 0; i < XI; ++i)
+      lds_dma16_at(xbase + (size_t)kt * 128, xo[i], __builtin_amdgcn_readfirstlane(base + (wave + i * NW) * 1024));
+#pragma unroll
+    for (int i = 0; i < WI; ++i)
+      lds_dma16_at(wbase + (size_t)kt * WB, wo[i], __builtin_amdgcn_readfirstlane(base + BM * 128 + (wave + i * NW) * 1024));
+  };
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int a = 0; a < TM; ++a)
+#pragma unroll
+    for (int b = 0; b < TN; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.0f;
+
+  const int xr = wm * WM + l32, wr = wn * WN + l32;
+  uint4 rx[TM][2], rw[TN][2];  // the next chunk's floats
+  Split sx[2][TM], sw[2][TN];
+  auto read = [&](const uint8_t* st, int q) {  // (split weights go straight to the chunk's operands)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int a = 0; a < TM; ++a) rx[a][i] = ldf(st + xr * 128 + f_swz(xr, 4 * q + 2 * half + i) * 16 + a * 32 * 128);
+      if constexpr (!WP) {
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+          rw[b][i] = ldf(st + BM * 128 + wr * 128 + f_swz(wr, 4 * q + 2 * half + i) * 16 + b * 32 * 128);
+      }
+    }
+    if constexpr (WP) {
+      const uint8_t* ws = st + BM * 128 + wr * 192 + ((2 * q + half) ^ ((wr >> 2) & 3)) * 16;
+#pragma unroll
+      for (int b = 0; b < TN; ++b)
+        sw[q][b] = Split{as_bf16x8(ldf(ws + b * 32 * 192)), as_bf16x8(ldf(ws + b * 32 * 192 + 64)),
+                         as_bf16x8(ldf(ws + b * 32 * 192 + 128))};
+    }
+  };
+  auto split = [&](int q) {
+#pragma unroll
+    for (int a = 0; a < TM; ++a) sx[q][a] = split3(rx[a][0], rx[a][1]);
+    if constexpr (!WP) {
+#pragma unroll
+      for (int b = 0; b < TN; ++b) sw[q][b] = split3(rw[b][0], rw[b][1]);
+    }
+  };
+  auto multiply = [&](const Split (&x)[TM], const Split (&w)[TN]) {
+    auto term = [&](bf16x8_t Split::*u, bf16x8_t Split::*v) {
+#pragma unroll
+      for (int b = 0; b < TN; ++b)
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[b].*u, x[a].*v, acc[a][b], 0, 0, 0);
+    };
+    term(&Split::l, &Split::h);
+    term(&Split::h, &Split::l);
+    term(&Split::m, &Split::m);
+    term(&Split::m, &Split::h);
+    term(&Split::h, &Split::m);
+    term(&Split::h, &Split::h);
+  };
+
+  // A chunk's matrix instructions, the next one's splitting between them from
+  // the fourth on (its floats are still on their way from LDS).
+  auto interleave = [] {
+    constexpr int kMat = 6 * TM * TN, kLead = 3, kVec = ((WP ? TM : TM + TN) * 44 + kMat - kLead - 1) / (kMat - kLead);
+    __builtin_amdgcn_sched_group_barrier(0x8, kLead, 0);  // matrix
+#pragma unroll
+    for (int i = kLead; i < kMat; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x2, kVec, 0);  // vector
+      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+    if (s < KT) issue(s, s);
+  wait_stage<LPS, S - 1>(min(S - 1, KT - 1));
+  __syncthreads();
+  read(smem, 0);
+  split(0);
+  read(smem, 1);
+  for (int kt0 = 0; kt0 < KT; kt0 += S) {
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+      const int kt = kt0 + u;
+      if (kt < KT) {
+        const uint8_t* sn = smem + (u + 1 == S ? 0 : u + 1) * kStage;
+        const bool more = kt + 1 < KT;
+        // chunk 0 of the stage; chunk 1 is split meanwhile
+        __builtin_amdgcn_sched_barrier(0);
+        split(1);
+        multiply(sx[0], sw[0]);
+        interleave();
+        wait_lgkmcnt0();
+        if (more) {
+          wait_stage<LPS, S - 2>(min(S - 2, KT - 2 - kt));
+          __syncthreads();  // stage kt + 1 visible; all of stage kt is in registers
+        }
+        // (after the last stage: old bytes, which nothing uses.  Under the branch
+        // the compiler moves the splitting there too, away from the products.)
+        read(sn, 0);
+        // chunk 1; the next stage's chunk 0 is split meanwhile
+        __builtin_amdgcn_sched_barrier(0);
+        split(0);
+        multiply(sx[1], sw[1]);
+        interleave();
+        if (kt + S < KT) issue(kt + S, u);
+        read(sn, 1);
+      }
+    }
+  }
+
+  // Epilogue.  A wave's 32 x WN block goes through its own LDS region.
+  __syncthreads();
+  constexpr int PITCH = WN * 4 + 16;
+  constexpr int CPR = WN / 4;  // 4-column chunks per row
+  constexpr int ITERS = 32 * CPR / 64;
+  uint8_t* stg = smem + wave * (32 * PITCH);
+  const int cc = lane % CPR, n = n0 + wn * WN + cc * 4;
+  const bool col_ok = n < N;
+  const int nc = col_ok ? n : 0;
+  const float4 bias = p.epi != Epi::None ? *reinterpret_cast<const float4*>(p.bias + nc) : make_float4(0, 0, 0, 0);
+#pragma unroll
+  for (int a = 0; a < TM; ++a) {
+    const int mb = m0 + wm * WM + a * 32;
+    float4 res[ITERS];
+    if (p.epi == Epi::BiasResidual) {
+#pragma unroll
+      for (int it = 0; it < ITERS; ++it)
+        res[it] = *reinterpret_cast<const float4*>(reinterpret_cast<const float*>(p.residual) +
+                                                   (size_t)min(mb + it * (64 / CPR) + lane / CPR, M - 1) * N + nc);
+    }
+#pragma unroll
+    for (int b = 0; b < TN; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<float4*>(stg + l32 * PITCH + (b * 32 + 8 * i + 4 * half) * 4) =
+            make_float4(acc[a][b][4 * i], acc[a][b][4 * i + 1], acc[a][b][4 * i + 2], acc[a][b][4 * i + 3]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+      const int r = it * (64 / CPR) + lane / CPR, m = mb + r;
+      const float4 v4 = *reinterpret_cast<const float4*>(stg + r * PITCH + cc * 16);
+      float v[4] = {v4.x, v4.y, v4.z, v4.w};
+      const float bb[4] = {bias.x, bias.y, bias.z, bias.w};
+      if (m < M && col_ok) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (!(fabsf(v[e]) <= 3.402823466e38f)) {
+            const float* xp = reinterpret_cast<const float*>(p.x) + (size_t)m * K;
+            const float* wp = reinterpret_cast<const float*>(p.w) + (size_t)(n + e) * K;
+            float d = 0.0f;
+#pragma unroll 1
+            for (int k = 0; k < K; ++k) d = fmaf(xp[k], wp[k], d);
+            v[e] = d;
+          }
+          v[e] += bb[e];
+        }
+        if (p.epi == Epi::BiasGelu) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+        } else if (p.epi == Epi::BiasResidual) {
+          v[0] += res[it].x; v[1] += res[it].y; v[2] += res[it].z; v[3] += res[it].w;
+        }
+        *reinterpret_cast<float4*>(reinterpret_cast<float*>(p.y) + (size_t)m * N + n) = make_float4(v[0], v[1], v[2], v[3]);
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+template <int BM, int BN, int WMW, int WNW, int S, bool WP>
+hipError_t launch_f32_tile(const GemmParams& p, hipStream_t s) {
+  constexpr int lds = std::max(S * (BM * 128 + BN * (WP ? 192 : 128)), WMW * WNW * 32 * (BN / WNW * 4 + 16));
+  static_assert(lds <= 160 * 1024, "LDS of a workgroup");
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_f32_kernel<BM, BN, WMW, WNW, S, WP>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (attr != hipSuccess) return attr;
+  const dim3 grid(((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN)), block(WMW * WNW * 64);
+  RLX_LOG_LAUNCH("gemm_f32_kernel", grid, block, lds, "tile=%dx%d stages=%d%s epi=%s M=%d%s N=%d K=%d", BM, BN, S,
+                 WP ? " split weights" : "", epi_name(p.epi), p.M, p.m_dev ? "(device)" : "", p.N, p.K);
+  hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, WMW, WNW, S, WP>), grid, block, lds, s, p);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_split_weights(const void* w, int N, int K, void* out, hipStream_t s) {
+  if (N <= 0 || K % 32 != 0) return hipErrorInvalidValue;
+  const int64_t n32 = (int64_t)N * (K / 32);
+  const dim3 grid((n32 * 4 + 255) / 256);
+  RLX_LOG_LAUNCH("split_weights_kernel", grid, dim3(256), 0, "N=%d K=%d", N, K);
+  hipLaunchKernelGGL(split_weights_kernel, grid, dim3(256), 0, s, reinterpret_cast<const float*>(w), n32,
+                     reinterpret_cast<uint16_t*>(out));
+  return hipGetLastError();
+}
+
+// (the limit on K keeps lane offsets in 32 bits)
+bool gemm_f32_supported(const GemmParams& p) {
+  return p.dtype == DType::F32 && p.quant == Quant::None && p.tile == 0 && p.x_head_rows == 0 && !p.x_stats &&
+         !p.res_stats && !p.y_stats && p.N % 64 == 0 && p.K % 64 == 0 && p.K <= (1 << 21);
+}
+
+// Measured (MI355X).  Error against float64, 2-norm, fp32 instructions / these:
+// 4352 x 384 x 1536 3.4e-7 / 2.9e-7, 256 x 4096 x 4096 7.7e-7 / 6.7e-7, 128 x 4096 x 14336
+// 1.8e-6 / 1.7e-6; the MiniLM forward 1.30e-7 / 1.29e-7.
+// Weights split here: 64 x 64 tiles, which share the least but split the fewest
+// floats per wave; us, fp32 instructions / these: 4352 x 1152 x 384 53 / 36, 256 x 4096 x
+// 4096 149 / 92, 128 x 4096 x 14336 493 / 286, 4352 x 384 x 384 18.3 / 17.4.
+// Weights split at create (encoder; M is the padded row count, about half of it
+// real): us per forward, 64 x 64 three stages / 64 x 64 two stages, four blocks per
+// CU / 128 x 128 / 256 x 128 for the wide projections (N >= 1024):
+//   batch 16 553 / 599 / - / -; batch 32 749 / 716 / 783 / 836; batch 64 994 / 955 / 966 /
+//   917; batch 256 3226 / 2988 / 2852 / 2971 (fp32 instructions: 625, 834, 1331, 4258);
+// for the narrow ones 64 x 64 three stages up to batch 64 (batch 32 716 against 749
+// with two), 128 x 128 at batch 256 (2783 against 2852).
+hipError_t launch_gemm_f32(const GemmParams& p, hipStream_t s) {
+  if (!p.w_split) return launch_f32_tile<64, 64, 2, 2, 3, false>(p, s);
+  if (p.N >= 1024) {
+    if (p.M >= 8192) return launch_f32_tile<256, 128, 4, 2, 2, true>(p, s);
+    if (p.M >= 4096) return launch_f32_tile<64, 64, 2, 2, 2, true>(p, s);
+  } else if (p.M >= 16384) {
+    return launch_f32_tile<128, 128, 2, 2, 2, true>(p, s);
+  }
+  return launch_f32_tile<64, 64, 2, 2, 3, true>(p, s);
+}
+
+}  // namespace rlx

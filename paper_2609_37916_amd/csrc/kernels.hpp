@@ -62,6 +62,8 @@ struct GemmParams {
   const float* y_gamma;
   bool res_scaled;
   float ln_eps;
+  // f32: the weights split into three bf16 parts by launch_split_weights ([N][K/32][3][32]), or null
+  const void* w_split;
   bool y_f32;            // bf16 x with an f32 output (and residual); not with the deferred-LayerNorm fields
 };
 // Names for the launch log.
@@ -115,6 +117,13 @@ hipError_t launch_gemm_big(const GemmParams& p, hipStream_t s);
 // The same for the encoder's dense calls (device-side row count, deferred LayerNorm).
 bool gemm_big_enc_supported(const GemmParams& p);
 hipError_t launch_gemm_big_enc(const GemmParams& p, hipStream_t s);
+
+// fp32 GEMM on the bf16 matrix cores (gemm_f32.hip).  launch_gemm takes it by
+// itself where its rule says so.
+bool gemm_f32_supported(const GemmParams& p);
+hipError_t launch_gemm_f32(const GemmParams& p, hipStream_t s);
+// f32 weights [N,K] (K a multiple of 32) -> their bf16 parts [N][K/32][3][32] (6 N K bytes).
+hipError_t launch_split_weights(const void* w, int N, int K, void* out, hipStream_t s);
 
 // GGUF blocks (type 2 Q4_0, 3 Q4_1, 8 Q8_0) of an [N, K] tensor -> the Int4
 // (Q4_0, z = 8), Int4M (Q4_1) or Int8G (Q8_0) layout (gguf.hip).

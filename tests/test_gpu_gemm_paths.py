@@ -372,3 +372,58 @@ def test_large_tile_epilogues_f32_output(rlx, epi):
     if epi == "residual":
         ref = ref + r
     assert_within(got, ref, gemm_tolerance(x, w, ref, out_bf16=False, pre=pre) + 2.0 ** -24 * np.abs(ref) * 4, epi)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 64, 64), (65, 128, 64), (130, 192, 448), (33, 64, 2048), (4100, 64, 128)])
+@pytest.mark.parametrize("epi", EPIS)
+def test_f32_product(rlx, epi, M, N, K):
+    """f32 operands over a range of magnitudes: the fp32 accumulation bound
+    (the three bf16 parts of a float are exact, the products left out are below
+    2^-26 of |x w| each)."""
+    rng = np.random.default_rng(600 + M + N + K)
+    x = (rng.normal(0, 1, (M, K)) * 2.0 ** rng.integers(-20, 20, (M, K))).astype(np.float32)
+    w = (rng.normal(0, 0.05, (N, K)) * 2.0 ** rng.integers(-20, 20, (N, K))).astype(np.float32)
+    b = rng.normal(0, 0.5, N).astype(np.float32)
+    r = rng.normal(0, 1, (M, N)).astype(np.float32)
+    y = rlx.dequant_matmul(_dev(x, torch.float32), _dev(w, torch.float32), bias=_dev(b, torch.float32),
+                           residual=_dev(r, torch.float32), epi=_epi_code(rlx, epi))
+    got = y.cpu().numpy()
+    ref = oracle.linear(x, w, None if epi == "none" else b)
+    pre = None
+    if epi == "gelu":
+        pre, ref = ref, oracle.gelu(ref)
+    if epi == "residual":
+        ref = ref + r
+    tol = gemm_tolerance(x, w, ref, out_bf16=False, weight_rel=3 * 2.0 ** -26, pre=pre)
+    assert_within(got, ref, tol + 2.0 ** -24 * np.abs(ref) * 4, f"f32 {epi} {M}x{N}x{K}")
+
+
+def test_f32_infinite_huge_and_nan(rlx):
+    """What the plain fp32 product gives: infinities of the weight's sign, NaN
+    where an operand is, finite results next to the largest floats."""
+    M, N, K = 4, 64, 128
+    rng = np.random.default_rng(9)
+    w = rng.normal(0, 1, (N, K)).astype(np.float32)
+    x = np.zeros((M, K), np.float32)
+    big = np.float32(np.finfo(np.float32).max)
+    x[0, 3], x[1, 5], x[2, 7] = np.inf, big, np.nan
+    w[:, 5] = rng.choice([0.5, -0.25, 2.0 ** -100], N)
+    got = rlx.dequant_matmul(_dev(x, torch.float32), _dev(w, torch.float32)).cpu().numpy()
+    assert np.array_equal(got[0], np.sign(w[:, 3]) * np.float32(np.inf))
+    assert np.array_equal(got[1], w[:, 5] * big)
+    assert np.all(np.isnan(got[2])) and np.all(got[3] == 0)
+
+
+@pytest.mark.parametrize("batch,seq", [(16, 64), (64, 64), (100, 100), (256, 64)])
+def test_f32_encoder_tiles(rlx, batch, seq):
+    """The fp32 encoder at padded row counts on both sides of its tile choice
+    (4096, 8192, 16384), short sequences in long rows."""
+    from workloads.device import encoder_kwargs, to_device
+    sp = workloads.spec("minilm_b4_s128_f32", batch=batch, seq=seq, layers=2, hidden=128, heads=4, ffn=1024, len_lo=1,
+                        len_hi=9, vocab=2000)
+    wl = workloads.make(sp, affine=True)
+    weights, inputs = to_device(wl)
+    enc = rlx.Encoder(**encoder_kwargs(sp), weights=weights)
+    got = enc.forward(inputs["input"], inputs["mask"]).cpu().numpy()
+    enc.close()
+    assert np.abs(got - oracle.encoder_forward(wl)).max() <= 1e-4
