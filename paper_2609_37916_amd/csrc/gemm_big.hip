@@ -490,20 +490,36 @@ hipError_t launch_big_q(const GemmParams& p, hipStream_t s) {
 
 }  // namespace
 
-// Where one round of 64 x 64 tiles does and K is short, launches are a few
-// microseconds of fixed cost and the smaller kernels' two K groups per block
-// (dense 1500 x 384 x 1536: 10.0 against 11.9 us here) or cheaper conversion
-// (int4 min 333 x 1088 x 960: 11.9 against 13.2) win; the int4 and group-16
-// layouts only below K = 1024, where those kernels convert a weight once per
-// block (int4 1500 x 384 x 1536: 21.2 against 19.3).
+// Calls of at most one round of 64 x 64 tiles that the four-wave kernels with 64 x
+// 64 tiles run faster, because two blocks share a CU or (dense) two groups of waves
+// share a stage's k (us, those / these tiles, M x N x K):
+//  * dense and int8, where K is short (dense 1500 x 384 x 1536 10.0 / 11.9) or N is not
+//    one for their 64 x 128 tiles (dense 500 x 384 x 14336 43.3 / 61.2, 1000 x 960 x
+//    8192 30.7 / 38.5; int8 128 x 640 x 8192 41.8 / 47.6, 40 x 4032 x 2560 16.2 / 17.9);
+//    with 64 x 128 tiles they lose (dense 597 x 1024 x 2240 16.6 / 14.0, int8 26.6 / 17.3);
+//  * int8 in groups alike, unless the scales of 64 rows don't fit their 32 KB of LDS
+//    or lie there at a pitch of a multiple of 16 banks (K = 2240, 35 banks: 18.4 /
+//    21.1; 4032, 63: 28.9 / 33.7; 3072, 48: 28.6 / 26.7; 4096, 64: 42.8 / 34.5; groups
+//    of 16, K = 2240: 19.4 / 21.9, 2560: 27.1 / 24.1, 4032: 31.8 / 35.5);
+//  * int4 below K = 1024 (min 333 x 1088 x 960 11.9 / 13.2): there those kernels convert
+//    a weight once per block (int4 1500 x 384 x 1536 21.2 / 19.3, 500 x 384 x 4096 68.2 /
+//    41.1).
+bool small_tiles_better(const GemmParams& p) {
+  if ((int64_t)((p.M + 63) / 64) * (p.N / 64) > 256) return false;
+  const bool narrow = p.N < 1024 || p.N % 128 != 0;
+  if (p.quant == Quant::None || p.quant == Quant::Int8) return p.K <= 2048 || narrow;
+  if (quant_int4(p.quant)) return p.K < 1024;
+  if (p.K < 1024 || (p.quant == Quant::Int8G && p.K <= 2048)) return true;
+  const int row = p.K / (p.quant == Quant::Int8G16 ? 16 : 32) * 2;  // bytes of a row's scales
+  return (narrow || 128 * (int64_t)row > 32 * 1024) && 64 * (int64_t)row <= 32 * 1024 && row / 4 % 16 != 0 &&
+         reinterpret_cast<uintptr_t>(p.scales) % 4 == 0;
+}
+
 bool gemm_big_supported(const GemmParams& p) {
   if (p.dtype != DType::BF16 || p.m_dev != nullptr || p.x_head_rows != 0 || p.x_stats || p.res_stats || p.y_stats ||
       p.tile != 0 || p.N % 64 != 0 || p.K % 64 != 0 || p.K > (1 << 22))
     return false;
-  const int64_t tiles64 = (int64_t)((p.M + 63) / 64) * (p.N / 64);
-  const bool long_conv = quant_int4(p.quant) || p.quant == Quant::Int8G16;
-  if (tiles64 <= 256 && p.K <= 2048 && !(long_conv && p.K >= 1024)) return false;
-  return true;
+  return !small_tiles_better(p);
 }
 
 // The encoder's narrow projections (output projection and FFN-down, N = hidden)

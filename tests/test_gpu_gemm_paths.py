@@ -327,8 +327,11 @@ def test_few_rows_infinite_and_huge_activations(rlx, scheme):
 # The large-tile kernel's edges: one shape for each of its tiles (256 x 256,
 # 256 x 128, 128 x 128, 128 x 64 or 64 x 128) with ragged last rows and columns, K of
 # one stage, fewer stages than the ring, and across the 256-k scale blocks.
+# The last three: few tiles and long rows, on either side of the line to the 64 x 64
+# tiles of the four-wave kernels (narrow or wide, group scales at LDS pitches of 34,
+# 32 and 36 banks).
 BIG_SHAPES = [(4001, 4160, 64), (2000, 4032, 128), (1000, 4032, 192), (257, 4160, 576), (65, 4160, 1088),
-              (1100, 1088, 320)]
+              (1100, 1088, 320), (70, 128, 2176), (65, 1024, 2304), (40, 192, 4096)]
 
 
 @pytest.mark.parametrize("scheme", SCHEMES + ["dense"])
