@@ -92,6 +92,22 @@ def test_benchmark_shape_sampled_rows(rlx, fx, fw):
     assert np.all(np.abs(got[rows] - ref) <= tol)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1025, 2048, 128),   # 578 64 x 64 tiles: 128 x 128, a last row tile of one row, one stage in a ring of four
+    (1040, 2048, 640),   # the same, five stages
+    (512, 4096, 384),    # 512 64 x 64 tiles, the most that stay 64 x 64; three stages, as many as are first issued
+    (1100, 4096, 256),   # 288 128 x 128 tiles: 256 x 128, two stages in a ring of three
+    (1100, 4096, 640),   # the same, five stages
+])
+@pytest.mark.parametrize("fx,fw", [(f, f) for f in FORMATS] + [("e4m3", "e2m1"), ("e3m2", "e5m2")])
+def test_tiles_bit_exact(rlx, fx, fw, M, N, K):
+    """Each tile size on inputs whose partial sums are exact: equal to the oracle."""
+    x, w = wmx.matmul_inputs(4000 + M + K + FORMATS.index(fx), M, N, K, fx, fw, exact=True)
+    got = _run(rlx, x, w, K)
+    ref = oracle.mx.scaled_matmul(x.packed, x.scales, fx, w.packed, w.scales, fw, K)
+    assert np.array_equal(got, ref.astype(np.float32)), (fx, fw, np.abs(got - ref).max())
+
+
 def test_wider_scale_range_and_single_row(rlx):
     """Scales spanning 2^-27 .. 2^27 (products far from 1), one row."""
     rng = np.random.default_rng(9)
