@@ -527,13 +527,17 @@ hipError_t launch_skinny(const GemmParams& p, hipStream_t s) {
 // tiles) above 768.  Dense rows are long enough for one tile per block, and
 // with 17 rows or more the first shape wins at every N (14336 x 4096, M = 32:
 // 34.9 / 41.9).  A deeper ring is slower (int4 M = 1, 4096 x 14336: 3 stages
-// 13.4, 6 14.9, 13 16.2 us).
+// 13.4, 6 14.9, 13 16.2 us).  int4 with up to 4 rows takes the two tiles with eight
+// waves: the unpacking gains from a CU's extra waves (four / eight waves, M x N x K:
+// 1 x 14336 x 4096 10.96 / 10.53, 1 x 14336 x 640 4.28 / 4.06, 4 x 14336 x 4096
+// 12.50 / 11.66), int8 loses (10.8 / 12.1).
 template <Quant Q, int MR>
 hipError_t launch_skinny_q(const GemmParams& p, hipStream_t s) {
   constexpr int kLds = 160 * 1024;
   constexpr SkStage L8 = sk_stage(Q, MR, 1, 8);
   const bool many = p.N / 16 > (MR <= 4 ? 768 : 256) && !(Q == Quant::None && MR > 16);
-  if (many) return launch_skinny<Q, MR, Q == Quant::None ? 1 : 2, 4, 2>(p, s);
+  constexpr int kManyWaves = quant_int4(Q) && MR <= 4 ? 8 : 4;
+  if (many) return launch_skinny<Q, MR, Q == Quant::None ? 1 : 2, kManyWaves, 2>(p, s);
   if constexpr (2 * L8.bytes <= kLds)
     return launch_skinny<Q, MR, 1, 8, 3 * L8.bytes <= kLds ? 3 : 2>(p, s);
   else  // 32 rows of dense or group-16 weights: stages of half the k

@@ -261,7 +261,7 @@ def test_f32_output_elementwise(rlx, case, epi):
 # and a half unit, more stages than the ring holds; N on both sides of the
 # launch-shape rule (256 and 768 tiles of 16 columns).
 FEW_ROW_SHAPES = [(1, 64, 128), (2, 128, 192), (5, 64, 1024), (9, 128, 1216), (17, 64, 4160), (32, 64, 640),
-                  (1, 64, 4096), (16, 4160, 576), (32, 4160, 320), (4, 12352, 704), (3, 4160, 128)]
+                  (1, 64, 4096), (16, 4160, 576), (32, 4160, 320), (4, 12352, 704), (3, 4160, 128), (2, 12352, 192)]
 
 
 @pytest.mark.parametrize("scheme", SCHEMES + ["dense"])
